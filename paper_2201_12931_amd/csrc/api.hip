@@ -294,9 +294,8 @@ size_t carve(hexmg_grid* g, char* base) {
   }
   const size_t nc = 3ull * g->lv[L - 1].nn;
   g->nc = (int)nc;
-  g->Abuf[0] = c.take<double>(nc * nc);
-  g->Abuf[1] = c.take<double>(nc * nc);
-  g->gjD = c.take<double>(2 * kGJBlock * kGJBlock);
+  g->Acoarse = c.take<double>(nc * nc);
+  g->inv_scratch = c.take<double>(spd_inverse_scratch((int)nc));
   g->Ecoarse = c.take<double>(g->lv[L - 1].ne);
   g->Ke64 = c.take<double>(576);
   g->Ke32 = c.take<float>(576);
@@ -1010,7 +1009,7 @@ int hexmg_grid_create(const hexmg_grid_desc* d, void* workspace, size_t bytes, v
   }
   g->density_set = false;
   g->profile = false;
-  g->Ainv = g->Abuf[0];
+  g->Ainv = g->Acoarse;
   g->last_stream = s;
   for (int i = 0; i < 8; ++i) {
     g->prof_ms[i] = 0.0;
@@ -1100,8 +1099,7 @@ int hexmg_set_density(hexmg_grid_t g, const double* rho, void* stream) {
   if (g->coarse_pending) HIP_TRY(hipStreamWaitEvent(s, g->ev_coarse, 0));
   // Coarsest level on the auxiliary stream: its moduli straight from level 0
   // (or the Galerkin stencil, which needs the levels above), assembly,
-  // Gauss-Jordan inverse, symmetrization; everything it reads is final when
-  // it is forked.  With density averaging it reads the caller's rho and is
+  // inverse; everything it reads is final when it is forked.  With density averaging it reads the caller's rho and is
   // forked before the SIMP kernel; the stream then waits for that read before
   // later work (which may overwrite rho) is ordered after this call.
   const int nc = g->nc;
@@ -1113,7 +1111,7 @@ int hexmg_set_density(hexmg_grid_t g, const double* rho, void* stream) {
     HIP_TRY(hipStreamWaitEvent(a, g->ev_fork, 0));
     const Level& C = g->lv[g->L - 1];
     if (g->galerkin) {
-      launch_dense_from_stencil(C, g->S64[g->L - 1], g->Abuf[0], a);
+      launch_dense_from_stencil(C, g->S64[g->L - 1], g->Acoarse, a);
     } else {
       const double* Ec = g->E64[0];
       if (g->L > 1) {
@@ -1123,14 +1121,10 @@ int hexmg_set_density(hexmg_grid_t g, const double* rho, void* stream) {
         if (early) HIP_TRY(hipEventRecord(g->ev_read, a));
         Ec = g->Ecoarse;
       }
-      launch_coarse_assemble(C, g->Ke64, Ec, g->Abuf[0], a);
+      launch_coarse_assemble(C, g->Ke64, Ec, g->Acoarse, a);
     }
-    double* inv = nullptr;
-    launch_gj_blocked(nc, g->Abuf[0], g->Abuf[1], g->gjD, &inv, a);
-    double* other = (inv == g->Abuf[0]) ? g->Abuf[1] : g->Abuf[0];
-    launch_symmetrize(nc, inv, other, a);
+    launch_spd_inverse(nc, g->Acoarse, g->inv_scratch, a);
     HIP_TRY(hipEventRecord(g->ev_coarse, a));
-    g->Ainv = other;
     g->coarse_pending = true;
     g->coarse_waited_valid = false;
     return 0;

@@ -240,7 +240,7 @@ void launch_sum_parts(const double* parts, int n, double* out, int nrhs, const i
 constexpr int kReduceBlocks = 1024;  // partial sums per reduction (fixed: deterministic)
 constexpr int kOcProbes = 32;       // Lagrange multipliers evaluated per OC pass
 constexpr int kBlock = 256;
-constexpr int kGJBlock = 64;  // pivot block of the blocked Gauss-Jordan inverse
+constexpr int kGJBlock = 64;  // pivot block of the coarsest inverse
 
 // ---- kernel launchers (kernels.hip) --------------------------------------
 // `act` (device, one int per right-hand side, may be null): right-hand sides
@@ -358,11 +358,10 @@ void launch_to64_dot(long long n, const float* u32, const double* r, double* z, 
                      const int* act, hipStream_t s);
 void launch_f64_to_f32(long long n, const double* a, float* b, int nrhs, const int* act, hipStream_t s);
 
-void launch_symmetrize(int n, const double* A, double* B, hipStream_t s);
-// Blocked Gauss-Jordan inverse of the n x n SPD matrix in A (B is the
-// ping-pong buffer, D 2 kGJBlock^2 scratch for the pivot-block inverses);
-// *result receives the buffer holding the inverse.  1 + ceil(n/64) launches.
-void launch_gj_blocked(int n, double* A, double* B, double* D, double** result, hipStream_t s);
+// Inverse of the n x n SPD row-major A in place, by block sweeps (inverse.hip);
+// scratch: spd_inverse_scratch(n) doubles.  2 + ceil(n/64) launches.
+size_t spd_inverse_scratch(int n);
+void launch_spd_inverse(int n, double* A, double* scratch, hipStream_t s);
 
 // Density filter and optimality criteria (topopt.hip)
 void launch_filter(int nx, int ny, int nz, double rmin, int adjoint, const double* in, double* out, double* tmp,
@@ -479,10 +478,10 @@ struct hexmg_grid {
   // V-cycle vectors per level: f (rhs), u (solution), t (ping-pong), r (residual)
   std::vector<double*> vf64, vu64, vt64, vr64;
   std::vector<float*> vf32, vu32, vt32, vr32;
-  double* Abuf[2];  // coarsest operator / Gauss-Jordan ping-pong
-  double* gjD;      // 2 kGJBlock^2
+  double* Acoarse;      // coarsest operator, then its inverse
+  double* inv_scratch;  // spd_inverse_scratch(nc) doubles
   double* Ecoarse;  // coarsest moduli for the coarsest operator (auxiliary stream)
-  double* Ainv;     // points at the buffer holding the symmetrized inverse
+  double* Ainv;     // the inverse (Acoarse)
   int nc;         // coarsest DOFs
   double* Ke64;   // 576
   float* Ke32;

@@ -358,8 +358,8 @@ __global__ void k_mask_inject(Level F, Level C, const uint8_t* __restrict__ mf, 
 }
 
 // ---------------------------------------------------------------------------
-// Coarsest level: dense A_c, in-place Gauss-Jordan inverse (SPD, so no pivoting),
-// and the direct solve e = A_c^{-1} f as a GEMV (Alg. 3, coarsest grid).
+// Coarsest level: dense A_c (its inverse: inverse.hip) and the direct solve e =
+// A_c^{-1} f as a GEMV (Alg. 3, coarsest grid).
 __global__ void k_coarse_assemble(Level C, const double* __restrict__ Ke, const double* __restrict__ E,
                                   double* __restrict__ A) {
   const int N = 3 * C.nn;
@@ -386,328 +386,6 @@ __global__ void k_coarse_assemble(Level C, const double* __restrict__ Ke, const 
     s += E[ei + C.nx * (ej + C.ny * ek)] * Ke[(3 * a + c1) * 24 + 3 * b + c2];
   }
   A[idx] = s;
-}
-
-// Blocked Gauss-Jordan.  For the pivot block K (rows/columns k0 .. k0+nb-1):
-//   D = A_KK^{-1};  X_J = D A_KJ (row panel, with X_K = D);
-//   B_K* = X,  B_IK = -A_IK D,  B_IJ = A_IJ - A_IK X_J,
-// which is nb scalar Gauss-Jordan steps applied at once.  A is read, B written.
-// The SPD coarse matrix (identity rows at fixed DOFs) needs no pivoting.
-//
-// Gauss-Jordan on a pivot block K of size b (b consecutive scalar steps at
-// once): with Q = A_KK^{-1}, every element takes
-//   a_ij <- z_ij - sum_h c_ih r_hj   (h = 0..b-1),
-// z = a with the rows and columns of K cleared, c_i = (a_i,k+h)_h for i not
-// in K and -e_i for i in K, r_j = Q (a_k+h,j)_h for j not in K and the column
-// Q e_j for j in K.  That leaves Q on K x K, Q A_Kj on the pivot rows,
-// -A_iK Q on the pivot columns and A_ij - A_iK Q A_Kj elsewhere.  The diagonal
-// blocks of an SPD matrix and of its Schur complements are SPD, so no
-// pivoting is needed.  For b = 4, Q comes from the 2x2 block form (inverse of
-// the leading 2x2 block, of its Schur complement, then the off-diagonal
-// blocks).
-__device__ inline void inv2(double a00, double a01, double a10, double a11, double (&q)[2][2]) {
-  // 1/det: hardware reciprocal and two Newton steps (each squares the
-  // relative error), shorter than the IEEE division on this latency-bound chain
-  const double det = a00 * a11 - a01 * a10;
-  double id = __builtin_amdgcn_rcp(det);
-  id = fma(id, fma(-det, id, 1.0), id);
-  id = fma(id, fma(-det, id, 1.0), id);
-  q[0][0] = a11 * id;
-  q[0][1] = -a01 * id;
-  q[1][0] = -a10 * id;
-  q[1][1] = a00 * id;
-}
-
-__device__ inline void inv4(const double (&p)[4][4], double (&q)[4][4]) {
-  double ai[2][2], x[2][2], y[2][2], sm[2][2], si[2][2];
-  inv2(p[0][0], p[0][1], p[1][0], p[1][1], ai);
-#pragma unroll
-  for (int r = 0; r < 2; ++r)
-#pragma unroll
-    for (int c = 0; c < 2; ++c) {
-      x[r][c] = ai[r][0] * p[0][2 + c] + ai[r][1] * p[1][2 + c];  // A^-1 B
-      y[r][c] = p[2 + r][0] * ai[0][c] + p[2 + r][1] * ai[1][c];  // C A^-1
-    }
-#pragma unroll
-  for (int r = 0; r < 2; ++r)
-#pragma unroll
-    for (int c = 0; c < 2; ++c) sm[r][c] = p[2 + r][2 + c] - (y[r][0] * p[0][2 + c] + y[r][1] * p[1][2 + c]);
-  inv2(sm[0][0], sm[0][1], sm[1][0], sm[1][1], si);
-#pragma unroll
-  for (int r = 0; r < 2; ++r)
-#pragma unroll
-    for (int c = 0; c < 2; ++c) {
-      q[2 + r][2 + c] = si[r][c];
-      q[r][2 + c] = -(x[r][0] * si[0][c] + x[r][1] * si[1][c]);
-      q[2 + r][c] = -(si[r][0] * y[0][c] + si[r][1] * y[1][c]);
-    }
-#pragma unroll
-  for (int r = 0; r < 2; ++r)
-#pragma unroll
-    for (int c = 0; c < 2; ++c) q[r][c] = ai[r][c] - (q[r][2] * y[0][c] + q[r][3] * y[1][c]);
-}
-
-typedef double d4 __attribute__((ext_vector_type(4)));
-
-// In-place inverse of the SPD 64x64 tile in LDS (row-major, padded rows; the
-// identity beyond its nb x nb block), by the block's 256 threads; written
-// transposed to DT (DT[j*64+i] = M_ij).  Block Gauss-Jordan with 16x16 pivot
-// blocks K (four steps, the unified update above with h = 0..15):
-//   Q = M_KK^{-1}                     16x16, one element per thread, by four
-//                                     steps of 4x4 pivot blocks (inv4);
-//   R = Q M_K*, with R_K = Q          on the matrix cores, one 16x16 tile per wave;
-//   M <- Z - C R                      on the matrix cores, 16 rows per wave,
-// with Z = M with the rows and columns of K cleared and C = M_*K, C_K = -I.
-// sR16: 16 rows of exchange space for R; sQ, pr, pc: small exchange buffers.
-template <int RR>
-__device__ inline void block_inverse(double (&sM)[kGJBlock][kGJBlock + 1], double (&sR16)[RR][kGJBlock + 1],
-                                     double (&sQ)[16][17], double (&pr)[2][4][16], double (&pc)[2][4][16],
-                                     double* __restrict__ DT) {
-  static_assert(RR >= 16 && kGJBlock == 64 && kBlock == 256, "four waves, 16x16 pivot blocks");
-  const int t = threadIdx.x, l = t & 63, w = t >> 6;
-  const int ti = t >> 4, tj = t & 15;  // element of the 16x16 pivot block
-  const int lr = l & 15, lk = l >> 4;  // matrix-core operand row / k of this lane
-#pragma unroll 1
-  for (int s = 0; s < 4; ++s) {
-    const int k0 = 16 * s;
-    // Q = M_KK^{-1}: Gauss-Jordan on 4x4 pivot blocks, one element per thread
-    double a = sM[k0 + ti][k0 + tj];
-#pragma unroll
-    for (int m = 0; m < 4; ++m) {
-      const int kb = 4 * m, par = m & 1;
-      const int hy = ti - kb, hx = tj - kb;
-      const bool rowk = hy >= 0 && hy < 4, colk = hx >= 0 && hx < 4;
-      if (rowk) pr[par][hy][tj] = a;
-      if (colk) pc[par][hx][ti] = a;
-      __syncthreads();
-      double pk[4][4], q[4][4];
-#pragma unroll
-      for (int h = 0; h < 4; ++h)
-#pragma unroll
-        for (int g = 0; g < 4; ++g) pk[h][g] = pr[par][h][kb + g];
-      inv4(pk, q);
-      double xg[4];
-#pragma unroll
-      for (int g = 0; g < 4; ++g) xg[g] = pr[par][g][tj];
-      double acc = (rowk || colk) ? 0.0 : a;
-#pragma unroll
-      for (int h = 0; h < 4; ++h) {
-        // Q e_hx as exact 0/1 weights (a select chain here becomes an indexed stack array)
-        const double qh = q[h][0] * (hx == 0 ? 1.0 : 0.0) + q[h][1] * (hx == 1 ? 1.0 : 0.0) +
-                          q[h][2] * (hx == 2 ? 1.0 : 0.0) + q[h][3] * (hx == 3 ? 1.0 : 0.0);
-        const double r = colk ? qh : q[h][0] * xg[0] + q[h][1] * xg[1] + q[h][2] * xg[2] + q[h][3] * xg[3];
-        const double c = rowk ? (hy == h ? -1.0 : 0.0) : pc[par][h][ti];
-        acc = fma(-c, r, acc);
-      }
-      a = acc;
-    }
-    sQ[ti][tj] = a;
-    __syncthreads();
-    // R = Q M_K* (tile w), R_K = Q
-    if (w == s) {
-#pragma unroll
-      for (int v = 0; v < 4; ++v) sR16[4 * v + lk][k0 + lr] = sQ[4 * v + lk][lr];
-    } else {
-      d4 r = d4{0.0, 0.0, 0.0, 0.0};
-#pragma unroll
-      for (int ks = 0; ks < 4; ++ks)
-        r = __builtin_amdgcn_mfma_f64_16x16x4f64(sQ[lr][4 * ks + lk], sM[k0 + 4 * ks + lk][16 * w + lr], r, 0, 0, 0);
-#pragma unroll
-      for (int v = 0; v < 4; ++v) sR16[4 * v + lk][16 * w + lr] = r[v];
-    }
-    __syncthreads();
-    // rows 16w..16w+15: M <- Z - C R
-    {
-      d4 y[4];
-      double cneg[4];
-#pragma unroll
-      for (int ct = 0; ct < 4; ++ct)
-#pragma unroll
-        for (int v = 0; v < 4; ++v)
-          y[ct][v] = (w == s || ct == s) ? 0.0 : sM[16 * w + 4 * v + lk][16 * ct + lr];
-#pragma unroll
-      for (int ks = 0; ks < 4; ++ks)
-        cneg[ks] = (w == s) ? (lr == 4 * ks + lk ? 1.0 : 0.0) : -sM[16 * w + lr][k0 + 4 * ks + lk];
-#pragma unroll
-      for (int ks = 0; ks < 4; ++ks)
-#pragma unroll
-        for (int ct = 0; ct < 4; ++ct)
-          y[ct] = __builtin_amdgcn_mfma_f64_16x16x4f64(cneg[ks], sR16[4 * ks + lk][16 * ct + lr], y[ct], 0, 0, 0);
-#pragma unroll
-      for (int ct = 0; ct < 4; ++ct)
-#pragma unroll
-        for (int v = 0; v < 4; ++v) sM[16 * w + 4 * v + lk][16 * ct + lr] = y[ct][v];
-    }
-    __syncthreads();
-  }
-#pragma unroll
-  for (int e = 0; e < kGJBlock * kGJBlock / kBlock; ++e) {
-    const int idx = t + kBlock * e, j = idx >> 6, i = idx & 63;
-    DT[j * kGJBlock + i] = sM[i][j];
-  }
-}
-
-// Inverse of the first diagonal block (later ones are formed by the panel
-// update that produces them).
-__global__ __launch_bounds__(kBlock) void k_gj_block_inv(int n, int k0, int nb, const double* __restrict__ A,
-                                                         double* __restrict__ DT) {
-  __shared__ double sM[kGJBlock][kGJBlock + 1], sR16[16][kGJBlock + 1], sQ[16][17];
-  __shared__ double pr[2][4][16], pc[2][4][16];
-#pragma unroll
-  for (int e = 0; e < kGJBlock * kGJBlock / kBlock; ++e) {
-    const int idx = threadIdx.x + kBlock * e, i = idx >> 6, j = idx & 63;
-    sM[i][j] = (i < nb && j < nb) ? A[(long long)(k0 + i) * n + k0 + j] : (i == j ? 1.0 : 0.0);
-  }
-  __syncthreads();
-  block_inverse(sM, sR16, sQ, pr, pc, DT);
-}
-
-// 64x64x64 product on the matrix cores: wave w accumulates rows 16w..16w+15
-// of L^T-stored-left times right, acc[t] holding the 16x16 output tile t
-// (columns 16t..16t+15).  v_mfma_f64_16x16x4f64 lane layout: the left operand
-// of lane l is element (row l%16, k l/16), the right one (k l/16, column l%16),
-// and output value v of lane l is element (row 4v + l/16, column l%16).
-template <int P>
-__device__ inline void mfma_64(const double (&sLT)[kGJBlock][P], const double (&sR)[kGJBlock][P], double sign,
-                               d4 (&acc)[4]) {
-  const int l = threadIdx.x & 63, w = threadIdx.x >> 6;
-#pragma unroll 4
-  for (int ks = 0; ks < kGJBlock / 4; ++ks) {
-    const int q = 4 * ks + (l >> 4);
-    const double a = sign * sLT[q][16 * w + (l & 15)];
-#pragma unroll
-    for (int t = 0; t < 4; ++t) acc[t] = __builtin_amdgcn_mfma_f64_16x16x4f64(a, sR[q][16 * t + (l & 15)], acc[t], 0, 0, 0);
-  }
-}
-
-// Row panel and update in one launch, grid (ceil(n / 64), ceil(n / 64)) of
-// 64x64 tiles (J, I).  The block of tile (I, J) first forms its own 64 columns
-// of the row panel, X_J = D A_KJ (X_K = D, from A_KK taken as the identity) --
-// the ceil(n/64)-fold recomputation costs 64^3 multiply-adds per tile, less
-// than a launch -- then
-//   B_ij = X[i-k0][j]                                          (I = K)
-//   B_ij = (J = K ? 0 : A_ij) - sum_q A[i][k0+q] X[q][j]        (otherwise).
-// Both products run on the binary64 matrix cores from LDS operands, D^T /
-// A_IK^T on the left (rows q, padded against bank conflicts) and A_KJ / X_J on
-// the right.  The block of the next diagonal tile (kb+1, kb+1) then inverts
-// its result in place and writes it transposed to DTnext, so the next step
-// needs no separate launch.
-__global__ __launch_bounds__(kBlock) void k_gj_panel_update(int n, int kb, int nb, const double* __restrict__ A,
-                                                            const double* __restrict__ DT,
-                                                            double* __restrict__ B, double* __restrict__ DTnext) {
-  static_assert(kGJBlock == 64 && kBlock == 256, "four waves of 16 output rows");
-  constexpr int P = kGJBlock + 1;
-  __shared__ double sL[kGJBlock][P];  // D^T, then A_IK^T
-  __shared__ double sR[kGJBlock][P];  // A_KJ (identity for J = K), then X_J
-  const int l = threadIdx.x & 63, w = threadIdx.x >> 6;
-  const int k0 = kb * kGJBlock, I = blockIdx.y, J = blockIdx.x;
-  const int i0 = I * kGJBlock, j0 = J * kGJBlock;
-  // row / column of output value v of tile t for this lane
-  auto orow = [&](int v) { return 16 * w + 4 * v + (l >> 4); };
-  auto ocol = [&](int t) { return 16 * t + (l & 15); };
-  // every global load of a stage is issued before the first LDS store
-  constexpr int kPer = kGJBlock * kGJBlock / kBlock;  // 16 elements per thread
-  {
-    double vl[kPer], vr[kPer];
-#pragma unroll
-    for (int m = 0; m < kPer; ++m) {
-      const int e = threadIdx.x + kBlock * m, r = e >> 6, c = e & 63;
-      vl[m] = (r < nb && c < nb) ? DT[r * kGJBlock + c] : 0.0;
-      vr[m] = (r < nb && j0 + c < n) ? ((J == kb) ? (r == c ? 1.0 : 0.0) : A[(long long)(k0 + r) * n + j0 + c])
-                                     : 0.0;
-    }
-#pragma unroll
-    for (int m = 0; m < kPer; ++m) {
-      const int e = threadIdx.x + kBlock * m, r = e >> 6, c = e & 63;
-      sL[r][c] = vl[m];
-      sR[r][c] = vr[m];
-    }
-  }
-  __syncthreads();
-  d4 acc[4];
-#pragma unroll
-  for (int t = 0; t < 4; ++t) acc[t] = d4{0.0, 0.0, 0.0, 0.0};
-  mfma_64<P>(sL, sR, 1.0, acc);  // acc = X_J
-  if (I == kb) {  // rows of the pivot block: B_K* = X
-#pragma unroll
-    for (int t = 0; t < 4; ++t)
-#pragma unroll
-      for (int v = 0; v < 4; ++v) {
-        const int i = i0 + orow(v), j = j0 + ocol(t);
-        if (i < n && j < n) B[(long long)i * n + j] = acc[t][v];
-      }
-    return;  // uniform per block
-  }
-  d4 y[4];
-  {
-    double va[kPer];
-#pragma unroll
-    for (int m = 0; m < kPer; ++m) {
-      const int e = threadIdx.x + kBlock * m, r = e >> 6, c = e & 63;  // A[i0 + r][k0 + c] -> sL[c][r]
-      va[m] = (i0 + r < n && c < nb) ? A[(long long)(i0 + r) * n + k0 + c] : 0.0;
-    }
-#pragma unroll
-    for (int t = 0; t < 4; ++t)
-#pragma unroll
-      for (int v = 0; v < 4; ++v) {
-        const int i = i0 + orow(v), j = j0 + ocol(t);
-        y[t][v] = (J != kb && i < n && j < n) ? A[(long long)i * n + j] : 0.0;
-      }
-    __syncthreads();  // every read of sL and sR is done
-#pragma unroll
-    for (int t = 0; t < 4; ++t)
-#pragma unroll
-      for (int v = 0; v < 4; ++v) sR[orow(v)][ocol(t)] = acc[t][v];
-#pragma unroll
-    for (int m = 0; m < kPer; ++m) {
-      const int e = threadIdx.x + kBlock * m, r = e >> 6, c = e & 63;
-      sL[c][r] = va[m];
-    }
-  }
-  __syncthreads();
-  mfma_64<P>(sL, sR, -1.0, y);  // y = A_IJ - A_IK X_J
-#pragma unroll
-  for (int t = 0; t < 4; ++t)
-#pragma unroll
-    for (int v = 0; v < 4; ++v) {
-      const int i = i0 + orow(v), j = j0 + ocol(t);
-      if (i < n && j < n) B[(long long)i * n + j] = y[t][v];
-    }
-  if (I == kb + 1 && J == kb + 1) {  // uniform per block
-    // the new diagonal tile to LDS (identity beyond its nbn x nbn block), then its inverse
-    __syncthreads();  // the product's reads of sR and sL are done
-    const int nbn = min(n - i0, kGJBlock);
-#pragma unroll
-    for (int t = 0; t < 4; ++t)
-#pragma unroll
-      for (int v = 0; v < 4; ++v) {
-        const int i = orow(v), j = ocol(t);
-        sR[i][j] = (i < nbn && j < nbn) ? y[t][v] : (i == j ? 1.0 : 0.0);
-      }
-    __shared__ double sQ[16][17], pr[2][4][16], pc[2][4][16];
-    __syncthreads();
-    block_inverse(sR, sL, sQ, pr, pc, DTnext);
-  }
-}
-
-// B = (A + A^T) / 2 by 32x32 tiles: tile (I, J) reads the mirror tile (J, I)
-// with rows along the lanes and transposes it through LDS, so both reads and
-// the write are row-contiguous.
-__global__ void k_symmetrize(int n, const double* __restrict__ A, double* __restrict__ B) {
-  __shared__ double mt[32][33];
-  const int i0 = 32 * blockIdx.y, j0 = 32 * blockIdx.x;
-  const int c = threadIdx.x & 31, r0 = threadIdx.x >> 5;  // 8 rows of 32 per pass
-#pragma unroll
-  for (int p = 0; p < 4; ++p) {  // mirror tile: A[j0 + r][i0 + c] -> mt[r][c]
-    const int r = r0 + 8 * p;
-    mt[r][c] = (j0 + r < n && i0 + c < n) ? A[(long long)(j0 + r) * n + i0 + c] : 0.0;
-  }
-  __syncthreads();
-#pragma unroll
-  for (int p = 0; p < 4; ++p) {
-    const int r = r0 + 8 * p, i = i0 + r, j = j0 + c;
-    if (i < n && j < n) B[(long long)i * n + j] = 0.5 * (A[(long long)i * n + j] + mt[c][r]);
-  }
 }
 
 template <typename T>
@@ -1361,23 +1039,6 @@ void launch_mask_inject(const Level& F, const Level& C, const uint8_t* mf, uint8
 void launch_coarse_assemble(const Level& C, const double* Ke, const double* E, double* A, hipStream_t s) {
   const int N = 3 * C.nn;
   k_coarse_assemble<<<dim3(blocks_for(N), N), kBlock, 0, s>>>(C, Ke, E, A);
-}
-void launch_gj_blocked(int n, double* A, double* B, double* D, double** result, hipStream_t s) {
-  double* buf[2] = {A, B};
-  double* dt[2] = {D, D + kGJBlock * kGJBlock};  // pivot inverses, alternating by step
-  int cur = 0;
-  const int t = (n + 63) / 64;
-  k_gj_block_inv<<<1, kBlock, 0, s>>>(n, 0, n < kGJBlock ? n : kGJBlock, A, dt[0]);
-  for (int kb = 0; kb < t; ++kb) {
-    const int k0 = kb * kGJBlock;
-    const int nb = (n - k0) < kGJBlock ? (n - k0) : kGJBlock;
-    k_gj_panel_update<<<dim3(t, t), kBlock, 0, s>>>(n, kb, nb, buf[cur], dt[kb & 1], buf[1 - cur], dt[(kb + 1) & 1]);
-    cur = 1 - cur;
-  }
-  *result = buf[cur];
-}
-void launch_symmetrize(int n, const double* A, double* B, hipStream_t s) {
-  k_symmetrize<<<dim3((n + 31) / 32, (n + 31) / 32), kBlock, 0, s>>>(n, A, B);
 }
 template <typename T>
 void launch_coarse_gemv(int n, const double* Ainv, const T* x, T* y, int nrhs, const int* act, hipStream_t s) {
