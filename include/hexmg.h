@@ -78,8 +78,8 @@ extern "C" {
 /* Storage of the Galerkin coarse stencils read by binary32 V-cycles (hexmg_grid_desc.stencil_storage) */
 #define HEXMG_STENCIL_F32 0  /* binary32 (default) */
 #define HEXMG_STENCIL_BF16 1 /* bfloat16: half the bytes, 8 significand bits, binary32's exponent range */
-#define HEXMG_STENCIL_F16 2  /* binary16: half the bytes, 11 significand bits, each node's row scaled by a
-                                power of two (kept per node) so that its largest coefficient is in [2^14, 2^15) */
+#define HEXMG_STENCIL_F16 2  /* binary16: half the bytes, 11 significand bits, each node's coefficients scaled by
+                                a power of two (kept per node) so that the largest is in [2^14, 2^15) */
 
 /* Coarse operators */
 #define HEXMG_COARSE_REDISCRETIZE 0 /* coarse element stiffness from the homogenized density (Sec. 4.2.2, default) */
@@ -104,9 +104,10 @@ typedef struct {
                                 Copied at hexmg_grid_create; coarse masks are injected
                                 (coarse node fixed iff the coincident fine node is). */
   int coarse_op;        /* HEXMG_COARSE_REDISCRETIZE | HEXMG_COARSE_GALERKIN.  Galerkin levels
-                           store 243 coefficients per node in both precisions (about
-                           2.9 kB per coarse node) and are applied as stencils; the
-                           cooperative coarse-cycle launch is not used with them. */
+                           store 126 coefficients per node (half of the symmetric 27-point
+                           stencil) in both precisions (about 1.5 kB per coarse node) and are
+                           applied as stencils; the cooperative coarse-cycle launch is not
+                           used with them. */
   int vcycle_both;      /* 0 (default): V-cycle vectors and Jacobi diagonals only in the solver's
                            precision (binary64 for HEXMG_FP64, binary32 otherwise), so
                            hexmg_vcycle accepts only that dtype; 1: both precisions (about

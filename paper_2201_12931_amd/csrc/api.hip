@@ -331,13 +331,15 @@ size_t carve(hexmg_grid* g, char* base) {
   g->S32.assign(L, nullptr);
   g->S16.assign(L, nullptr);
   g->Sexp.assign(L, nullptr);
-  g->Gc = c.take<double>(8 * 576);
+  g->Gc = c.take<double>(kChildMatrices);
   if (g->galerkin) {
     // binary64 stencils for the set-up (and binary64 V-cycles); the binary32
     // V-cycle's copy in its storage precision
     const int store = g->desc.stencil_storage;
+    g->gal_flag = c.take<uint8_t>(g->lv[1].nn);
+    g->gal_list = c.take<int>(g->lv[1].nn);
     for (int l = 1; l < L; ++l) {
-      const size_t nq = 243ull * g->lv[l].nn;
+      const size_t nq = (size_t)kStencilCoefs * g->lv[l].nn;
       g->S64[l] = c.take<double>(nq);
       if (store == HEXMG_STENCIL_F32) g->S32[l] = c.take<float>(nq);  // binary32 K u at any precision
       if (v32 && store != HEXMG_STENCIL_F32) g->S16[l] = c.take<uint16_t>(nq);
@@ -1042,7 +1044,7 @@ int hexmg_grid_create(const hexmg_grid_desc* d, void* workspace, size_t bytes, v
   if (hipMemcpyAsync(g->Ke64, Ke, sizeof(Ke), hipMemcpyHostToDevice, s) != hipSuccess ||
       hipMemcpyAsync(g->Ke32, Kf, sizeof(Kf), hipMemcpyHostToDevice, s) != hipSuccess)
     return cleanup(fail(HEXMG_ERR_DEVICE, "copy of the element matrix failed"));
-  g->Gc_host.resize(8 * 576);
+  g->Gc_host.resize(kChildMatrices);
   galerkin_child_matrices(Ke, g->Gc_host.data());
   if (hipMemcpyAsync(g->Gc, g->Gc_host.data(), g->Gc_host.size() * sizeof(double), hipMemcpyHostToDevice, s) !=
       hipSuccess)
@@ -1055,6 +1057,10 @@ int hexmg_grid_create(const hexmg_grid_desc* d, void* workspace, size_t bytes, v
   }
   for (int l = 1; l < g->L; ++l) launch_mask_inject(g->lv[l - 1], g->lv[l], g->mask[l - 1], g->mask[l], s);
   g->desc.fixed_mask = nullptr;  // copied; do not keep the caller's pointer
+  if (g->galerkin) {
+    g->gal_count = galerkin_flag(g->lv[0], g->lv[1], g->gal_flag, g->gal_list, g->active, s);
+    if (g->gal_count < 0) return cleanup(fail(HEXMG_ERR_DEVICE, "listing the nodes next to the supports failed"));
+  }
   if (hipStreamSynchronize(s) != hipSuccess || hipGetLastError() != hipSuccess)
     return cleanup(fail(HEXMG_ERR_DEVICE, "grid set-up kernels failed"));
   *out = g;
@@ -1146,7 +1152,8 @@ int hexmg_set_density(hexmg_grid_t g, const double* rho, void* stream) {
       launch_modulus_from_mean(g->lv[l - 1], g->lv[l], g->E64[l - 1], 2.0, g->E64[l], g->E32[l], s);
   }
   if (g->galerkin) {  // Eq. 23 products, level by level, as stencils
-    launch_galerkin_first(g->lv[0], g->lv[1], g->E64[0], g->Gc, g->Ke64, g->S64[1], g->S32[1], s);
+    launch_galerkin_first(g->lv[0], g->lv[1], g->E64[0], g->Gc, g->Ke64, g->gal_flag, g->gal_list, g->gal_count,
+                          g->S64[1], g->S32[1], s);
     for (int l = 1; l + 1 < g->L; ++l)
       launch_galerkin_coarsen(g->lv[l], g->lv[l + 1], g->S64[l], g->S64[l + 1], g->S32[l + 1], s);
     for (int l = 1; l < g->L; ++l)

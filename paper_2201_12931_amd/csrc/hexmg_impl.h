@@ -128,6 +128,19 @@ __device__ inline int xcd_band_index(int l, int T, long long first) {
   for (int k = 0; k < c; ++k) start += ((k - r0) & 7) < rem;
   return start + (l >> 3);
 }
+// The launch's blocks (x dimension) in slabs of `slab` consecutive blocks,
+// each slab in XCD bands (xcd_band_index): with a slab of about one plane of
+// the grid, the blocks that read the same rows of the other level run on one
+// L2, and the next slab's band (the next plane) re-reads rows the same L2 has
+// just held.
+__device__ inline int xcd_band_block(int slab) {
+  const int n = (int)gridDim.x, b = (int)blockIdx.x;
+  const int s0 = b - b % slab;
+  return s0 + xcd_band_index(b - s0, min(slab, n - s0), (long long)n * blockIdx.y + s0);
+}
+// A slab of about one plane of `per_plane` blocks, a multiple of 8.
+inline int band_slab(long long per_plane) { return (int)per_plane > 8 ? (per_plane + 7) / 8 * 8 : 8; }
+
 template <typename T>
 struct StreamTask {
   Level L;
@@ -388,10 +401,16 @@ void launch_oc_apply(long long n, const double* x, const double* dc, const doubl
 // dv_e = [passive_e == 0] / (number of such elements); count: one int of scratch
 void launch_volume_weights(long long n, const uint8_t* passive, int* count, double* dv, hipStream_t s);
 
-// Galerkin coarse operators (galerkin.hip): 27-point block stencils,
-// coefficient (9 o + 3 ci + cj) of node n at S[(9 o + 3 ci + cj) * nn + n].
+// Galerkin coarse operators (galerkin.hip): the stored half of the 27-point block
+// stencils (offsets o = 13..26), coefficient (9 (o - 13) + 3 ci + cj) of node n at
+// S[(9 (o - 13) + 3 ci + cj) * nn + n].
+constexpr int kStencilCoefs = 126;
+constexpr int kChildMatrices = 8 * 576 + 36 * 72;  // doubles of galerkin_child_matrices
+// level-1 nodes next to fixed fine DOFs: flag per node, their list; returns their
+// number (synchronises s), -1 on error
+int galerkin_flag(const Level& F, const Level& C, uint8_t* flag, int* list, int* count, hipStream_t s);
 void launch_galerkin_first(const Level& F, const Level& C, const double* E, const double* G, const double* Ke,
-                           double* S64, float* S32, hipStream_t s);
+                           const uint8_t* flag, const int* list, int count, double* S64, float* S32, hipStream_t s);
 void launch_galerkin_coarsen(const Level& F, const Level& C, const double* Sf, double* S64, float* S32,
                              hipStream_t s);
 template <typename T>
@@ -407,7 +426,7 @@ void launch_stencil_to16(int store, const Level& L, const double* S64, uint16_t*
                          hipStream_t s);
 void launch_stencil_diag(const Level& L, const double* S, double omega, double* wd64, float* wd32, hipStream_t s);
 void launch_dense_from_stencil(const Level& C, const double* S, double* A, hipStream_t s);
-void galerkin_child_matrices(const double* Ke, double* G);  // host: 8 x 576
+void galerkin_child_matrices(const double* Ke, double* G);  // host: kChildMatrices doubles
 
 // The coarse part of the V-cycle in one cooperative launch (coarse.hip):
 // levels, operators and vectors of one precision.  f[ls] holds the restricted
@@ -493,6 +512,9 @@ struct hexmg_grid {
   std::vector<uint16_t*> S16;  // 16-bit coefficients (stencil_storage != HEXMG_STENCIL_F32)
   std::vector<int8_t*> Sexp;   // binary16 rows' scale exponents
   double* Gc = nullptr;
+  uint8_t* gal_flag = nullptr;  // level-1 nodes next to fixed fine DOFs: flag, list and number of them
+  int* gal_list = nullptr;
+  int gal_count = 0;
   std::vector<double> Gc_host;
   hexmg::HaarCoef<double> hq64;
   hexmg::HaarCoef<float> hq32;

@@ -106,19 +106,6 @@ __global__ void k_jacobi_first_from64(long long n, const float* __restrict__ wdi
   }
 }
 
-// The launch's blocks (x dimension) in slabs of `slab` consecutive blocks,
-// each slab in XCD bands (xcd_band_index): with a slab of about one plane of
-// the grid, the blocks that read the same rows of the other level run on one
-// L2, and the next slab's band (the next plane) re-reads rows the same L2 has
-// just held.
-__device__ inline int xcd_band_block(int slab) {
-  const int n = (int)gridDim.x, b = (int)blockIdx.x;
-  const int s0 = b - b % slab;
-  return s0 + xcd_band_index(b - s0, min(slab, n - s0), (long long)n * blockIdx.y + s0);
-}
-// A slab of about one plane of `per_plane` blocks, a multiple of 8.
-inline int band_slab(long long per_plane) { return (int)std::max<long long>(8, (per_plane + 7) / 8 * 8); }
-
 // Coarse right-hand side f_c = M_c P^T r (see restrict_node); with wdc set,
 // also the coarse level's first Jacobi sweep from zero, tc = wdc * f_c.
 // (bx, rhs): the workgroup's place in a launch of (ceil(C.nn / kBlock), nrhs).

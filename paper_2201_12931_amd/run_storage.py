@@ -61,7 +61,7 @@ def main():
             code, inf = grid.solve(f_d, u, rtol=args.rtol, maxit=args.maxit)
             ms.append(inf[0]["ms_solve"])
             info = inf[0]
-        nq = sum(243 * (g.nx // 2 ** l + 1) * (g.ny // 2 ** l + 1) * (g.nz // 2 ** l + 1) for l in range(1, levels))
+        nq = sum(126 * (g.nx // 2 ** l + 1) * (g.ny // 2 ** l + 1) * (g.nz // 2 ** l + 1) for l in range(1, levels))
         word = {hexmg.STENCIL_F32: 4, hexmg.STENCIL_BF16: 2, hexmg.STENCIL_F16: 2}[store]
         r = {"status": code, "iterations": info["iterations"], "rel_res_true": info["rel_res_true"],
              "compliance": info["compliance"], "solve_ms": sorted(ms)[len(ms) // 2], "setup_ms": setup_ms,
