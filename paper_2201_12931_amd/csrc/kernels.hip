@@ -430,9 +430,16 @@ __global__ void k_reduce_final(const double* __restrict__ partials, double* __re
 // flight that the ~70 k partials of a large level take a few microseconds.
 constexpr int kSumThreads = 1024;
 // The per-iteration CG vector passes: each of the kReduceBlocks workgroups
-// walks contiguous ranges of kVecChunk elements, kReduceBlocks ranges apart
-// (measured faster than an element-wise grid stride at the same launch).
-constexpr long long kVecChunk = 4096;
+// walks contiguous ranges of vec_chunk(n) elements, kReduceBlocks ranges apart
+// (measured faster than an element-wise grid stride at the same launch).  At
+// most 4096 elements, and as many as give every workgroup the same number of
+// ranges: with 4096 throughout, 28 k unknowns kept 7 of the 1024 workgroups busy
+// and 12.8 M left a last round on 6% of them.
+__device__ inline long long vec_chunk(long long n) {
+  const unsigned m = (unsigned)n, rounds = (m + (kReduceBlocks * 4096u - 1)) / (kReduceBlocks * 4096u);
+  const unsigned ranges = kReduceBlocks * rounds;
+  return ((m + ranges - 1) / ranges + kBlock - 1) / kBlock * kBlock;
+}
 __global__ __launch_bounds__(kSumThreads) void k_sum_parts(const double* __restrict__ parts, int n,
                                                            double* __restrict__ out, const int* __restrict__ act) {
   if (act && !act[blockIdx.x]) return;
@@ -586,8 +593,9 @@ __device__ __forceinline__ void update_r_first_block(long long n, const double* 
   if (f32) f32 += off;
   if (t) t += off;
   double acc = 0.0;
-  for (long long b0 = (long long)bx * kVecChunk; b0 < n; b0 += (long long)gx * kVecChunk) {
-    const long long e = min(b0 + kVecChunk, n);
+  const long long chunk = vec_chunk(n);
+  for (long long b0 = bx * chunk; b0 < n; b0 += gx * chunk) {
+    const long long e = min(b0 + chunk, n);
 #pragma unroll 4
     for (long long i = b0 + threadIdx.x; i < e; i += kBlock) {
       const double ri = r[i] - alpha * (double)q[i];
@@ -682,6 +690,7 @@ __device__ __forceinline__ void update_px_block(long long n, const double* __res
                                                 float* __restrict__ p32b, int bx, int rhs) {
   constexpr int gx = kReduceBlocks;
   if (!active[rhs]) return;
+  const long long chunk = vec_chunk(n);
   double rzs = 0.0;
   for (int i = threadIdx.x; i < nrz; i += kBlock) rzs += rz_partials[(long long)nrz * rhs + i];
   const double rz = block_sum_all(rzs);
@@ -704,8 +713,8 @@ __device__ __forceinline__ void update_px_block(long long n, const double* __res
     p32b += off;
     if (parity) {
       const double a_odd = s[kAlphaP], a_even = s[kAlphaP + 1];
-      for (long long b0 = (long long)bx * kVecChunk; b0 < n; b0 += (long long)gx * kVecChunk) {
-        const long long e = min(b0 + kVecChunk, n);
+      for (long long b0 = bx * chunk; b0 < n; b0 += gx * chunk) {
+        const long long e = min(b0 + chunk, n);
 #pragma unroll 4
         for (long long i = b0 + threadIdx.x; i < e; i += kBlock) {
           const double po = (double)p32[i], pe = (double)p32b[i];
@@ -717,8 +726,8 @@ __device__ __forceinline__ void update_px_block(long long n, const double* __res
         }
       }
     } else {
-      for (long long b0 = (long long)bx * kVecChunk; b0 < n; b0 += (long long)gx * kVecChunk) {
-        const long long e = min(b0 + kVecChunk, n);
+      for (long long b0 = bx * chunk; b0 < n; b0 += gx * chunk) {
+        const long long e = min(b0 + chunk, n);
 #pragma unroll 4
         for (long long i = b0 + threadIdx.x; i < e; i += kBlock)
           p32b[i] = (float)((double)z[i] + beta * (double)p32[i]);
@@ -727,8 +736,8 @@ __device__ __forceinline__ void update_px_block(long long n, const double* __res
     return;
   }
   p += off;
-  for (long long b0 = (long long)bx * kVecChunk; b0 < n; b0 += (long long)gx * kVecChunk) {
-    const long long e = min(b0 + kVecChunk, n);
+  for (long long b0 = bx * chunk; b0 < n; b0 += gx * chunk) {
+    const long long e = min(b0 + chunk, n);
     if (p32) {
 #pragma unroll 4
       for (long long i = b0 + threadIdx.x; i < e; i += kBlock) {
