@@ -291,8 +291,7 @@ int hexmg_apply_passive(long long n, const uint8_t *passive, double *x, void *st
  * receives lambda, change_host (host, may be NULL) the largest |x_new - x|
  * (the change that Alg. 4's stop test reads) and volume_host (host, may be
  * NULL) dv^T x_new, the constrained volume of the new design.
- * Synchronises the stream once per bisection pass (32 multipliers per pass),
- * and once more when change_host or volume_host is given. */
+ * Synchronises the stream once, after the last kernel. */
 int hexmg_oc_update(hexmg_grid_t grid, const double *x, const double *dc, const double *dv, double volfrac,
                     double move, double eta, double *x_new, double *lambda_host, double *change_host,
                     double *volume_host, void *stream);

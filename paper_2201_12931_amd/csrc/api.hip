@@ -325,7 +325,7 @@ size_t carve(hexmg_grid* g, char* base) {
   g->active = c.take<int>(R);
   g->repl = c.take<int>(R);
   g->oc_partials = c.take<double>((size_t)kReduceBlocks * kOcProbes);
-  g->oc_vol = c.take<double>(kOcProbes);
+  g->oc_state = c.take<OcState>(1);
   g->galerkin = g->desc.coarse_op == HEXMG_COARSE_GALERKIN && L > 1;
   g->S64.assign(L, nullptr);
   g->S32.assign(L, nullptr);
@@ -1902,46 +1902,22 @@ int hexmg_oc_update(hexmg_grid_t g, const double* x, const double* dc, const dou
     return fail(HEXMG_ERR_INVALID, "need 0 < volfrac < 1, 0 < move <= 1, 0 < eta <= 1");
   hipStream_t s = (hipStream_t)stream;
   const long long n = g->lv[0].ne;
-  // bisection on log lambda, kOcProbes interior probes per pass
-  double lo = std::log(1e-12), hi = std::log(1e12);
-  const double rel_tol = 1e-12;
+  // bisection on log lambda, kOcProbes interior points per pass: every pass
+  // narrows the bracket by kOcProbes + 1, so their number is known here
+  const double lo = std::log(1e-12), hi = std::log(1e12), rel_tol = 1e-12;
   int passes = 0;
-  while (std::exp(hi - lo) - 1.0 > rel_tol && passes < 64) {
-    OcProbes pw;
-    double lp[kOcProbes];
-    for (int p = 0; p < kOcProbes; ++p) {
-      lp[p] = lo + (hi - lo) * (p + 1) / (kOcProbes + 1);
-      pw.v[p] = std::exp(-eta * lp[p]);
-    }
-    launch_oc_probe(n, x, dc, dv, eta, move, pw, g->oc_partials, g->oc_vol, s);
-    HIP_TRY(hipMemcpyAsync(g->host_scalars, g->oc_vol, kOcProbes * sizeof(double), hipMemcpyDeviceToHost, s));
-    HIP_TRY(hipStreamSynchronize(s));
-    // the pinned mirror holds 8*kScalars doubles
-    static_assert(kOcProbes <= 8 * kScalars, "pinned buffer too small");
-    double nlo = lo, nhi = hi;
-    for (int p = 0; p < kOcProbes; ++p) {
-      if (g->host_scalars[p] > volfrac) {
-        nlo = lp[p];
-      } else {
-        nhi = lp[p];
-        break;
-      }
-    }
-    if (!std::isfinite(g->host_scalars[0])) return fail(HEXMG_ERR_NONFINITE, "non-finite OC volume");
-    lo = nlo;
-    hi = nhi;
-    ++passes;
-  }
-  const double lam = std::exp(0.5 * (lo + hi));
-  launch_oc_apply(n, x, dc, dv, eta, move, std::exp(-eta * 0.5 * (lo + hi)), x_new, g->oc_partials, g->oc_vol, s);
+  for (double width = hi - lo; std::exp(width) - 1.0 > rel_tol && passes < 64; width /= kOcProbes + 1) ++passes;
+  launch_oc_update(n, x, dc, dv, volfrac, eta, move, lo, hi, passes, x_new, g->oc_partials, g->oc_state, s);
   HIP_TRY(hipGetLastError());
-  if (change_host || volume_host) {
-    HIP_TRY(hipMemcpyAsync(g->host_scalars, g->oc_vol, 2 * sizeof(double), hipMemcpyDeviceToHost, s));
-    HIP_TRY(hipStreamSynchronize(s));
-    if (change_host) *change_host = g->host_scalars[0];
-    if (volume_host) *volume_host = g->host_scalars[1];
-  }
-  if (lambda_host) *lambda_host = lam;
+  static_assert(sizeof(OcState) <= 8 * kScalars * sizeof(double), "pinned buffer too small");
+  HIP_TRY(hipMemcpyAsync(g->host_scalars, g->oc_state, sizeof(OcState), hipMemcpyDeviceToHost, s));
+  HIP_TRY(hipStreamSynchronize(s));
+  OcState st;
+  std::memcpy(&st, g->host_scalars, sizeof(st));
+  if (st.bad != 0.0) return fail(HEXMG_ERR_NONFINITE, "non-finite OC volume");
+  if (lambda_host) *lambda_host = st.lambda;
+  if (change_host) *change_host = st.change;
+  if (volume_host) *volume_host = st.volume;
   return 0;
 }
 

@@ -389,15 +389,16 @@ void launch_gravity_load(const Level& L, const double* rho, double g, const doub
                          hipStream_t s);
 void launch_gravity_sensitivity(const Level& L, const double* u, double coef, double* dc, hipStream_t s);
 void launch_apply_passive(long long n, const uint8_t* passive, double* x, hipStream_t s);
-struct OcProbes {
-  double v[kOcProbes];  // lambda_p^(-eta)
+// State of an OC update on the device: the bracket of log lambda, whether a volume
+// was not finite (x_new is then not written), and the results.
+struct OcState {
+  double lo, hi, bad, change, volume, lambda;
 };
-void launch_oc_probe(long long n, const double* x, const double* dc, const double* dv, double eta, double move,
-                     const OcProbes& lam_pow, double* partials, double* vol, hipStream_t s);
-// x_new at the final multiplier; out[0] = max |x_new - x|, out[1] = dv . x_new
-// (partials: 2 kReduceBlocks doubles of scratch)
-void launch_oc_apply(long long n, const double* x, const double* dc, const double* dv, double eta, double move,
-                     double lam_pow, double* xn, double* partials, double* out, hipStream_t s);
+// The OC update from the bracket [lo, hi], narrowed `passes` times by kOcProbes
+// points each (partials: kReduceBlocks * kOcProbes doubles of scratch), results in *st.
+void launch_oc_update(long long n, const double* x, const double* dc, const double* dv, double volfrac, double eta,
+                      double move, double lo, double hi, int passes, double* xn, double* partials, OcState* st,
+                      hipStream_t s);
 // dv_e = [passive_e == 0] / (number of such elements); count: one int of scratch
 void launch_volume_weights(long long n, const uint8_t* passive, int* count, double* dv, hipStream_t s);
 
@@ -544,7 +545,7 @@ struct hexmg_grid {
   int* repl;      // per right-hand side: 1 where this iteration replaces the residual (HEXMG_MIXED32)
   double* host_ring;  // pinned: 3 slots of kScalars * max_nrhs doubles (results in flight)
   double* oc_partials;  // kReduceBlocks x kOcProbes
-  double* oc_vol;       // kOcProbes
+  hexmg::OcState* oc_state;
   double* host_scalars;  // pinned host mirror
   bool density_set;
   hipStream_t last_stream;
