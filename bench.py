@@ -31,16 +31,16 @@ HBM_PEAK_GBS = 8000.0
 
 # Kernel families the library times per launch, and their algorithmic HBM
 # bytes per level-0 launch: every vector read or written once (4 or 8 B per
-# DOF), the moduli once (4 or 8 B per element), the support bits once (1 B per
-# node).
+# DOF; omega/D is one value per node, a third of that), the moduli once (4 or 8
+# B per element), the support bits once (1 B per node).
 FAMILY_BYTES = {
-    "smooth_f32": (16, 4),    # read u, f, omega/D, write u
-    "smooth1_f32": (12, 4),   # the sweep on the first sweep from zero, formed from f and omega/D: read f, omega/D, write u
+    "smooth_f32": (12 + 4 / 3, 4),    # read u, f, omega/D, write u
+    "smooth1_f32": (8 + 4 / 3, 4),   # the sweep on the first sweep from zero, formed from f and omega/D: read f, omega/D, write u
     "residual_f32": (12, 4),  # read u, f, write r
     "apply_f32": (8, 4),      # read u, write A u
     "apply_f64": (16, 8),     # binary64 solves; the mixed solver's K p reads a binary32 p: (12, 8), set in main()
-    "smooth_f64": (32, 8),
-    "smooth1_f64": (24, 8),
+    "smooth_f64": (24 + 8 / 3, 8),
+    "smooth1_f64": (16 + 8 / 3, 8),
     "residual_f64": (24, 8),
 }
 

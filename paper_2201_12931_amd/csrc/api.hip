@@ -242,6 +242,13 @@ void make_levels(const hexmg_grid_desc* d, std::vector<Level>& lv) {
     L.nn = L.nxn * L.nyn * L.nzn;
     L.ne = L.nx * L.ny * L.nz;
     L.mask = nullptr;
+    // omega 0 = automatic: 0.6 with re-discretized coarse operators, 0.5 with
+    // Galerkin ones (on black-and-white designs the Galerkin hierarchy has
+    // lambda_max(D^-1 A) of 4-6, where 0.6 lets damped Jacobi amplify the
+    // highest modes)
+    const bool galerkin = d->coarse_op == HEXMG_COARSE_GALERKIN && d->levels > 1;
+    L.omega = d->omega > 0.0 ? d->omega : (galerkin ? 0.5 : 0.6);
+    L.per_dof = galerkin && l > 0;
     lv.push_back(L);
   }
 }
@@ -278,14 +285,14 @@ size_t carve(hexmg_grid* g, char* base) {
     g->E32[l] = c.take<float>(lv.ne);
     g->mask[l] = c.take<uint8_t>(lv.nn);
     if (v64) {
-      g->wd64[l] = c.take<double>(N);
+      g->wd64[l] = c.take<double>(lv.per_dof ? N : lv.nn);
       g->vf64[l] = c.take<double>(N * R);
       g->vu64[l] = c.take<double>(N * R);
       g->vt64[l] = c.take<double>(N * R);
       g->vr64[l] = c.take<double>(N * R);
     }
     if (v32) {
-      g->wd32[l] = c.take<float>(N);
+      g->wd32[l] = c.take<float>(lv.per_dof ? N : lv.nn);
       g->vf32[l] = c.take<float>(N * R);
       g->vu32[l] = c.take<float>(N * R);
       g->vt32[l] = c.take<float>(N * R);
@@ -723,7 +730,6 @@ void vcycle_level(hexmg_grid* g, VView<T>& v, int l, const T* f, T* out, int nrh
         [](const Batch<GemvTask<T>>& b, hipStream_t st) { launch_coarse_gemv_batch<T>(b, st); });
     return;
   }
-  const long long N = 3ll * L.nn;
   const int nu = g->desc.smooth_sweeps;
   T* buf[2] = {v.t[l], out};
   int cur = 0;
@@ -734,7 +740,7 @@ void vcycle_level(hexmg_grid* g, VView<T>& v, int l, const T* f, T* out, int nrh
     const T* wdl = v.wd[l];
     T* t0 = buf[0];
     emit_launch(g, st_down(l, 0), s,
-                [=](hipStream_t st) { launch_jacobi_first<T>(N, wdl, f, t0, nrhs, act, st); });
+                [=](hipStream_t st) { launch_jacobi_first<T>(L, wdl, f, t0, nrhs, act, st); });
   }
   for (int it = 1; it < nu; ++it) {
     g->stage = st_down(l, it);
@@ -1160,16 +1166,11 @@ int hexmg_set_density(hexmg_grid_t g, const double* rho, void* stream) {
       if (g->S16[l]) launch_stencil_to16(d.stencil_storage, g->lv[l], g->S64[l], g->S16[l], g->Sexp[l], s);
     if (int e = fork_coarsest()) return e;
   }
-  // omega 0 = automatic: 0.6 with re-discretized coarse operators, 0.5 with
-  // Galerkin ones (on black-and-white designs the Galerkin hierarchy has
-  // lambda_max(D^-1 A) of 4-6, where 0.6 lets damped Jacobi amplify the
-  // highest modes)
-  const double omega = d.omega > 0.0 ? d.omega : (g->galerkin ? 0.5 : 0.6);
-  if (g->galerkin) {
-    launch_diag(g->lv[0], g->Ke64, g->E64[0], omega, g->wd64[0], g->wd32[0], s);
-    for (int l = 1; l < g->L; ++l) launch_stencil_diag(g->lv[l], g->S64[l], omega, g->wd64[l], g->wd32[l], s);
-  } else {
-    for (int l = 0; l < g->L; ++l) launch_diag(g->lv[l], g->Ke64, g->E64[l], omega, g->wd64[l], g->wd32[l], s);
+  for (int l = 0; l < g->L; ++l) {
+    if (g->lv[l].per_dof)
+      launch_stencil_diag(g->lv[l], g->S64[l], g->wd64[l], g->wd32[l], s);
+    else
+      launch_diag(g->lv[l], g->Ke64, g->E64[l], g->wd64[l], g->wd32[l], s);
   }
   if (early) HIP_TRY(hipStreamWaitEvent(s, g->ev_read, 0));
   HIP_TRY(hipGetLastError());

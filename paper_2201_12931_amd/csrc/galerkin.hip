@@ -471,13 +471,13 @@ __global__ __launch_bounds__(kBlock) void k_stencil(Level L, SP S, const int8_t*
   y[b] = MODE == kApply ? Au : (MODE == kSmooth ? ub + wb * (fb - Au) : fb - Au);
 }
 
-__global__ void k_stencil_diag(Level L, const double* __restrict__ S, double omega, double* __restrict__ wd64,
+__global__ void k_stencil_diag(Level L, const double* __restrict__ S, double* __restrict__ wd64,
                                float* __restrict__ wd32) {
   const int n = blockIdx.x * kBlock + threadIdx.x;
   if (n >= L.nn) return;
 #pragma unroll
   for (int c = 0; c < 3; ++c) {
-    const double w = omega / S[(long long)(4 * c) * L.nn + n];
+    const double w = L.omega / S[(long long)(4 * c) * L.nn + n];
     if (wd64) wd64[3ll * n + c] = w;  // either output may be absent
     if (wd32) wd32[3ll * n + c] = (float)w;
   }
@@ -572,8 +572,8 @@ template void launch_stencil<double>(int, const Level&, const double*, const dou
 template void launch_stencil<float>(int, const Level&, const float*, const float*, const float*, const float*,
                                     float*, int, const int*, hipStream_t, const LaunchTimer&);
 
-void launch_stencil_diag(const Level& L, const double* S, double omega, double* wd64, float* wd32, hipStream_t s) {
-  k_stencil_diag<<<blocks_for(L.nn), kBlock, 0, s>>>(L, S, omega, wd64, wd32);
+void launch_stencil_diag(const Level& L, const double* S, double* wd64, float* wd32, hipStream_t s) {
+  k_stencil_diag<<<blocks_for(L.nn), kBlock, 0, s>>>(L, S, wd64, wd32);
 }
 
 void launch_dense_from_stencil(const Level& C, const double* S, double* A, hipStream_t s) {

@@ -25,6 +25,8 @@ struct Level {
   int nn;             // node count
   int ne;             // element count
   const uint8_t* mask;  // per-node support bits (device)
+  double omega;         // Jacobi damping (the sweep's factor at fixed DOFs, whose diagonal is 1)
+  int per_dof;          // omega / diag held per DOF (Galerkin levels >= 1) instead of per node
 };
 
 // Haar-basis block coefficients of the unit element (already divided by 64):
@@ -271,7 +273,7 @@ void launch_gather_apply_u32(const Level& L, const double* Ke, const double* E, 
 enum { kApply = 0, kSmooth = 1, kResidual = 2, kSmoothFirst = 3 };
 
 template <typename T>
-void launch_jacobi_first(long long n, const T* wdinv, const T* f, T* u, int nrhs, const int* act, hipStream_t s);
+void launch_jacobi_first(const Level& L, const T* wdinv, const T* f, T* u, int nrhs, const int* act, hipStream_t s);
 // binary32 first sweep from a binary64 right-hand side: f32 = (float) r, u = wdinv f32
 void launch_jacobi_first_from64(long long n, const float* wdinv, const double* r, float* f32, float* u, int nrhs,
                                 const int* act, hipStream_t s);
@@ -292,8 +294,7 @@ void launch_modulus_from_mean(const Level& F, const Level& C, const double* Ef, 
 // element, blocks of blk^3 fine elements; v0 = densities or fine moduli).
 void launch_coarsest_moduli(const Level& F, const Level& C, int blk, const double* v0, bool density, double E0,
                             double Emin, double p, double scale, double* Ec, hipStream_t s);
-void launch_diag(const Level& L, const double* Ke, const double* E, double omega, double* wdinv64,
-                 float* wdinv32, hipStream_t s);
+void launch_diag(const Level& L, const double* Ke, const double* E, double* wdinv64, float* wdinv32, hipStream_t s);
 void launch_mask_default(const Level& L, uint8_t* mask, hipStream_t s);
 void launch_mask_inject(const Level& F, const Level& C, const uint8_t* mf, uint8_t* mc, hipStream_t s);
 void launch_or_flags(int n, const int* flags, int* out, hipStream_t s);
@@ -425,7 +426,7 @@ void launch_stencil16(int store, int mode, const Level& L, const uint16_t* S16, 
                       const LaunchTimer& t = {});
 void launch_stencil_to16(int store, const Level& L, const double* S64, uint16_t* S16, int8_t* sexp,
                          hipStream_t s);
-void launch_stencil_diag(const Level& L, const double* S, double omega, double* wd64, float* wd32, hipStream_t s);
+void launch_stencil_diag(const Level& L, const double* S, double* wd64, float* wd32, hipStream_t s);
 void launch_dense_from_stencil(const Level& C, const double* S, double* A, hipStream_t s);
 void galerkin_child_matrices(const double* Ke, double* G);  // host: kChildMatrices doubles
 
@@ -492,7 +493,9 @@ struct hexmg_grid {
   std::vector<double*> rho;      // homogenized densities (level 0: copy of the input)
   std::vector<double*> E64;      // element moduli incl. the 2^l size factor
   std::vector<float*> E32;
-  std::vector<double*> wd64;     // omega / diag(A_l)
+  // omega / diag(A_l): one value per node (the three components of a node have the
+  // same diagonal; fixed DOFs take Level::omega), per DOF on Galerkin levels >= 1
+  std::vector<double*> wd64;
   std::vector<float*> wd32;
   std::vector<uint8_t*> mask;
   // V-cycle vectors per level: f (rhs), u (solution), t (ping-pong), r (residual)

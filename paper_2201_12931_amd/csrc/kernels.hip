@@ -86,12 +86,14 @@ __global__ __launch_bounds__(kBlock) void k_gather(Level L, const T* __restrict_
 
 // First sweep from a zero guess: u = omega D^{-1} f.
 template <typename T>
-__global__ void k_jacobi_first(long long n, const T* __restrict__ wdinv, const T* __restrict__ f,
-                               T* __restrict__ u, const int* __restrict__ act) {
+__global__ void k_jacobi_first(Level L, const T* __restrict__ wdinv, const T* __restrict__ f, T* __restrict__ u,
+                               const int* __restrict__ act) {
   if (act && !act[blockIdx.y]) return;
-  const long long i = (long long)blockIdx.x * kBlock + threadIdx.x;
-  const long long off = n * blockIdx.y;  // right-hand side
-  if (i < n) u[off + i] = wdinv[i] * f[off + i];
+  const int i = blockIdx.x * kBlock + threadIdx.x, n = 3 * L.nn;
+  const long long off = (long long)n * blockIdx.y;  // right-hand side
+  if (i >= n) return;
+  const int node = i / 3, c = i % 3;
+  u[off + i] = (((L.mask[node] >> c) & 1) ? T(L.omega) : wdinv[node]) * f[off + i];
 }
 
 __global__ void k_jacobi_first_from64(long long n, const float* __restrict__ wdinv, const double* __restrict__ r,
@@ -102,7 +104,7 @@ __global__ void k_jacobi_first_from64(long long n, const float* __restrict__ wdi
   if (i < n) {
     const float fv = (float)r[off + i];
     f32[off + i] = fv;
-    u[off + i] = wdinv[i] * fv;
+    u[off + i] = wdinv[(unsigned)i / 3] * fv;  // r is zero at fixed DOFs
   }
 }
 
@@ -298,36 +300,28 @@ __global__ void k_modulus_from_mean(Level F, Level C, const double* __restrict__
   E32[e] = (float)E;
 }
 
+// omega / diag(A) per node: the element stiffness of a cube has one diagonal entry
+// for all its DOFs, so a node's three components share theirs (fixed DOFs take
+// L.omega where the sweep is applied).  One value per node instead of three takes
+// 8 (16) of a binary32 (binary64) sweep's 53 (106) bytes per node away: the level-0 sweeps
+// are bound by their bytes, and the solve at 768x384x384 went from 128.4 to 123.2
+// ms, the binary64 one at 256x128x128 from 11.50 to 11.09.
 __global__ void k_diag(Level L, const double* __restrict__ Ke, const double* __restrict__ E,
-                       double omega, double* __restrict__ wd64, float* __restrict__ wd32) {
+                       double* __restrict__ wd64, float* __restrict__ wd32) {
   const int n = blockIdx.x * kBlock + threadIdx.x;
   if (n >= L.nn) return;
   int i, j, k;
   node_coords(L, n, i, j, k);
-  double d0 = 0, d1 = 0, d2 = 0;
+  double d = 0;
   for (int a = 0; a < 8; ++a) {
     const int ax = a & 1, ay = (a >> 1) & 1, az = a >> 2;
     const int ei = i - ax, ej = j - ay, ek = k - az;
     if (ei < 0 || ei >= L.nx || ej < 0 || ej >= L.ny || ek < 0 || ek >= L.nz) continue;
-    const double Ee = E[ei + L.nx * (ej + L.ny * ek)];
-    d0 += Ee * Ke[(3 * a + 0) * 25];
-    d1 += Ee * Ke[(3 * a + 1) * 25];
-    d2 += Ee * Ke[(3 * a + 2) * 25];
+    d += E[ei + L.nx * (ej + L.ny * ek)] * Ke[0];
   }
-  const int mk = L.mask[n];
-  const double w0 = omega / ((mk & 1) ? 1.0 : d0);
-  const double w1 = omega / ((mk & 2) ? 1.0 : d1);
-  const double w2 = omega / ((mk & 4) ? 1.0 : d2);
-  if (wd64) {  // either output may be absent (the grid holds one precision)
-    wd64[3ll * n] = w0;
-    wd64[3ll * n + 1] = w1;
-    wd64[3ll * n + 2] = w2;
-  }
-  if (wd32) {
-    wd32[3ll * n] = (float)w0;
-    wd32[3ll * n + 1] = (float)w1;
-    wd32[3ll * n + 2] = (float)w2;
-  }
+  const double w = L.omega / d;
+  if (wd64) wd64[n] = w;  // either output may be absent (the grid holds one precision)
+  if (wd32) wd32[n] = (float)w;
 }
 
 __global__ void k_mask_default(Level L, uint8_t* __restrict__ mask) {
@@ -604,9 +598,9 @@ __device__ __forceinline__ void update_r_first_block(long long n, const double* 
       if constexpr (sizeof(TW) == 4) {
         const float fv = (float)ri;
         f32[i] = fv;
-        if (t) t[i] = wdinv[i] * fv;
+        if (t) t[i] = wdinv[(unsigned)i / 3] * fv;  // r is zero at fixed DOFs
       } else {
-        if (t) t[i] = wdinv[i] * ri;
+        if (t) t[i] = wdinv[(unsigned)i / 3] * ri;
       }
     }
   }
@@ -804,7 +798,7 @@ __global__ void k_replace_r(Level L, const double* __restrict__ f, const double*
     acc += ri * ri;
     const float fv = (float)ri;
     f32[i] = fv;
-    if (t) t[i] = wdinv[i] * fv;
+    if (t) t[i] = wdinv[node] * fv;
   }
   acc = block_sum(acc);
   if (threadIdx.x == 0) rr_partials[blockIdx.x] = acc;
@@ -963,12 +957,12 @@ void launch_gather_apply_u32(const Level& L, const double* Ke, const double* E, 
 }
 
 template <typename T>
-void launch_jacobi_first(long long n, const T* wdinv, const T* f, T* u, int nrhs, const int* act, hipStream_t s) {
-  k_jacobi_first<T><<<dim3(blocks_for(n), nrhs), kBlock, 0, s>>>(n, wdinv, f, u, act);
+void launch_jacobi_first(const Level& L, const T* wdinv, const T* f, T* u, int nrhs, const int* act, hipStream_t s) {
+  k_jacobi_first<T><<<dim3(blocks_for(3ll * L.nn), nrhs), kBlock, 0, s>>>(L, wdinv, f, u, act);
 }
-template void launch_jacobi_first<double>(long long, const double*, const double*, double*, int, const int*,
+template void launch_jacobi_first<double>(const Level&, const double*, const double*, double*, int, const int*,
                                           hipStream_t);
-template void launch_jacobi_first<float>(long long, const float*, const float*, float*, int, const int*,
+template void launch_jacobi_first<float>(const Level&, const float*, const float*, float*, int, const int*,
                                          hipStream_t);
 void launch_jacobi_first_from64(long long n, const float* wdinv, const double* r, float* f32, float* u, int nrhs,
                                 const int* act, hipStream_t s) {
@@ -1021,9 +1015,8 @@ void launch_coarsest_moduli(const Level& F, const Level& C, int blk, const doubl
                             double Emin, double p, double scale, double* Ec, hipStream_t s) {
   k_coarsest_moduli<<<C.ne, kBlock, 0, s>>>(F, C, blk, v0, density ? 1 : 0, E0, Emin, p, scale, Ec);
 }
-void launch_diag(const Level& L, const double* Ke, const double* E, double omega, double* wdinv64,
-                 float* wdinv32, hipStream_t s) {
-  k_diag<<<blocks_for(L.nn), kBlock, 0, s>>>(L, Ke, E, omega, wdinv64, wdinv32);
+void launch_diag(const Level& L, const double* Ke, const double* E, double* wdinv64, float* wdinv32, hipStream_t s) {
+  k_diag<<<blocks_for(L.nn), kBlock, 0, s>>>(L, Ke, E, wdinv64, wdinv32);
 }
 void launch_mask_default(const Level& L, uint8_t* mask, hipStream_t s) {
   k_mask_default<<<blocks_for(L.nn), kBlock, 0, s>>>(L, mask);

@@ -81,9 +81,10 @@ __device__ inline void gather_node(const Level& L, const T* __restrict__ Ke, con
     y[b + 1] = Au1;
     y[b + 2] = Au2;
   } else if (MODE == kSmooth) {
-    y[b] = u[b] + wdinv[b] * (f[b] - Au0);
-    y[b + 1] = u[b + 1] + wdinv[b + 1] * (f[b + 1] - Au1);
-    y[b + 2] = u[b + 2] + wdinv[b + 2] * (f[b + 2] - Au2);
+    const T w = wdinv[n], wf = T(L.omega);
+    y[b] = u[b] + ((mk & 1) ? wf : w) * (f[b] - Au0);
+    y[b + 1] = u[b + 1] + ((mk & 2) ? wf : w) * (f[b + 1] - Au1);
+    y[b + 2] = u[b + 2] + ((mk & 4) ? wf : w) * (f[b + 2] - Au2);
   } else {
     y[b] = f[b] - Au0;
     y[b + 1] = f[b + 1] - Au1;
@@ -131,9 +132,12 @@ __device__ inline void restrict_node(const Level& F, const Level& C, const T* __
   fc[3ll * m + 1] = f1;
   fc[3ll * m + 2] = f2;
   if (wdc) {
-    tc[3ll * m] = wdc[3ll * m] * f0;
-    tc[3ll * m + 1] = wdc[3ll * m + 1] * f1;
-    tc[3ll * m + 2] = wdc[3ll * m + 2] * f2;
+    // (f is zero at fixed DOFs, so a node's one factor serves them too)
+    const T* w = wdc + (C.per_dof ? 3ll * m : m);
+    const int st = C.per_dof ? 1 : 0;
+    tc[3ll * m] = w[0] * f0;
+    tc[3ll * m + 1] = w[st] * f1;
+    tc[3ll * m + 2] = w[2 * st] * f2;
   }
 }
 

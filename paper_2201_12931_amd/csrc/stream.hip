@@ -245,12 +245,13 @@ __device__ __forceinline__ void stream_tile(const Level& L, const HaarCoef<T>& q
   const int vbytes = (int)(3 * plane * (long long)sizeof(T));   // one plane of a nodal vector
   const int ubytes = (int)(3 * plane * (long long)sizeof(TU));  // one plane of u
   const int ebytes = (int)(eplane * (long long)sizeof(T));      // one layer of moduli
+  const int wbytes = (int)(plane * (long long)sizeof(T));       // one plane of omega/D (one value per node)
   const int mbytes = (int)plane;                                 // one plane of support bits
 
   // Row r of this wave is node row j0 + r; rows 0..R are read, rows 0..R-1 own
   // element rows and (when inside the tile's output window) output rows.
   // Byte offsets inside a plane; kOutside where the row is not read / written.
-  int offu[R + 1], offm[R + 1], offe[R], offo[R], offmo[R];
+  int offu[R + 1], offm[R + 1], offw[R + 1], offe[R], offo[R], offmo[R], offwo[R];
 #pragma unroll
   for (int r = 0; r <= R; ++r) {
     const int jr = j0 + r;
@@ -258,12 +259,14 @@ __device__ __forceinline__ void stream_tile(const Level& L, const HaarCoef<T>& q
     const bool in = col_in && jr >= 0 && jr < L.nyn;
     offu[r] = in ? n * (3 * (int)sizeof(TU)) : kOutside;
     offm[r] = in ? n : kOutside;
+    offw[r] = in ? n * (int)sizeof(T) : kOutside;
     if (r < R) {
       offe[r] = (col_elem && jr >= 0 && jr < L.ny) ? (i + L.nx * jr) * (int)sizeof(T) : kOutside;
       const int rt = w * R + r;
       const bool out = lane_out && rt >= 1 && rt <= kOutRows && jr < L.nyn;
       offo[r] = out ? n * (3 * (int)sizeof(T)) : kOutside;
       offmo[r] = out ? n : kOutside;
+      offwo[r] = out ? n * (int)sizeof(T) : kOutside;
     }
   }
 
@@ -273,22 +276,22 @@ __device__ __forceinline__ void stream_tile(const Level& L, const HaarCoef<T>& q
   // Plane buffers alternate by parity (A holds the planes kc0-1, kc0+1, ...,
   // B the others), so the pipeline never copies a plane between registers.
   TU uA[R + 1][3], uB[R + 1][3];
-  T wA[FIRST ? R + 1 : 1][3], wB[FIRST ? R + 1 : 1][3];  // omega/D of the input planes (FIRST)
+  T wA[FIRST ? R + 1 : 1], wB[FIRST ? R + 1 : 1];  // omega/D of the input planes (FIRST)
   T uo[R][3];
   int mA[R + 1], mB[R + 1];
   T EA[R], EB[R];
   __shared__ T xch[2][W][3][64];  // [parity][wave][xyz][lane]: node values for the next wave
   // Only planes kc0-1..kc1 and element layers kc0-1..kc1-1 are needed; the
   // pipeline's requests outside them are given empty resources (no traffic).
-  auto load_plane = [&](int kk, TU (&u)[R + 1][3], T (&wv)[FIRST ? R + 1 : 1][3], int (&m)[R + 1]) {
+  auto load_plane = [&](int kk, TU (&u)[R + 1][3], T (&wv)[FIRST ? R + 1 : 1], int (&m)[R + 1]) {
     const bool pin = kk >= 0 && kk < L.nzn && kk <= kc1;
     if constexpr (FIRST) {
       const Rsrc ru = plane_rsrc(fg + 3 * plane * (pin ? kk : 0), pin ? vbytes : 0);
-      const Rsrc rw = plane_rsrc(wg + 3 * plane * (pin ? kk : 0), pin ? vbytes : 0);
+      const Rsrc rw = plane_rsrc(wg + plane * (pin ? kk : 0), pin ? wbytes : 0);
 #pragma unroll
       for (int r = 0; r <= R; ++r) {
         load3(ru, offu[r], u[r]);
-        load3(rw, offu[r], wv[r]);
+        wv[r] = load1(rw, offw[r], T(0));
       }
     } else {
       const Rsrc ru = plane_rsrc(ug + 3 * plane * (pin ? kk : 0), pin ? ubytes : 0);
@@ -333,7 +336,7 @@ __device__ __forceinline__ void stream_tile(const Level& L, const HaarCoef<T>& q
 
   // Inputs of the epilogue of iteration kk (output plane kk-1): support bits,
   // f and omega/D.
-  auto load_out = [&](int kk, int (&mo)[R], T (&fo)[R][3], T (&wo)[R][3]) {
+  auto load_out = [&](int kk, int (&mo)[R], T (&fo)[R][3], T (&wo)[R]) {
     const bool out_plane = kk - 1 >= kc0 && kk - 1 < kc1;
     const long long po = plane * (out_plane ? kk - 1 : 0);
     {
@@ -347,9 +350,9 @@ __device__ __forceinline__ void stream_tile(const Level& L, const HaarCoef<T>& q
       for (int r = 0; r < R; ++r) load3(rf, offo[r], fo[r]);
     }
     if (MODE == kSmooth || FIRST) {
-      const Rsrc rw = plane_rsrc(wg + 3 * po, out_plane ? vbytes : 0);
+      const Rsrc rw = plane_rsrc(wg + po, out_plane ? wbytes : 0);
 #pragma unroll
-      for (int r = 0; r < R; ++r) load3(rw, offo[r], wo[r]);
+      for (int r = 0; r < R; ++r) wo[r] = load1(rw, offwo[r], T(0));
     }
   };
 
@@ -357,9 +360,9 @@ __device__ __forceinline__ void stream_tile(const Level& L, const HaarCoef<T>& q
   // kk-1 and the output of plane kk-1.
   // Fin/Tin: the previous plane's face modes and the previous layer's top-face
   // modes; Fout/Tout receive this plane's and this layer's.
-  auto body = [&](int kk, const TU (&uc)[R + 1][3], const T (&wc)[FIRST ? R + 1 : 1][3], const int (&mc)[R + 1],
+  auto body = [&](int kk, const TU (&uc)[R + 1][3], const T (&wc)[FIRST ? R + 1 : 1], const int (&mc)[R + 1],
                   const T (&Ec)[R], const int (&mo)[R],
-                  const T (&fo)[R][3], const T (&wo)[R][3], const T (&Fin)[R][4][3], T (&Fout)[R][4][3],
+                  const T (&fo)[R][3], const T (&wo)[R], const T (&Fin)[R][4][3], T (&Fout)[R][4][3],
                   const T (&Tin)[R][4][3], T (&Tout)[R][4][3]) {
     const bool out_plane = kk - 1 >= kc0 && kk - 1 < kc1;
     const Rsrc ry = plane_rsrc(yg + 3 * plane * (out_plane ? kk - 1 : 0), out_plane ? vbytes : 0);
@@ -375,7 +378,7 @@ __device__ __forceinline__ void stream_tile(const Level& L, const HaarCoef<T>& q
         // is not contracted into the additions that consume it
 #pragma clang fp contract(off)
 #pragma unroll
-        for (int c = 0; c < 3; ++c) ue[r][c] = wc[r][c] * ue[r][c];
+        for (int c = 0; c < 3; ++c) ue[r][c] = wc[r] * ue[r][c];
       }
       if (MASKIN && __any(mc[r] != 0)) {
 #pragma unroll
@@ -408,7 +411,9 @@ __device__ __forceinline__ void stream_tile(const Level& L, const HaarCoef<T>& q
           v[c] = Au;
           if (DOT && out_plane && offo[r] != kOutside) dot += (double)uo[r][c] * (double)Au;
         } else if (MODE == kSmooth || FIRST) {
-          v[c] = uo[r][c] + wo[r][c] * (fo[r][c] - Au);
+          // fixed DOFs take omega; where f and u vanish there, any factor does
+          const T wr = MASKIN ? select_bit(mo[r], c, T(L.omega), wo[r]) : wo[r];
+          v[c] = uo[r][c] + wr * (fo[r][c] - Au);
           if (DOT && out_plane && offo[r] != kOutside) dot += (double)fo[r][c] * (double)v[c];
         } else
           v[c] = fo[r][c] - Au;
@@ -524,10 +529,10 @@ __device__ __forceinline__ void stream_tile(const Level& L, const HaarCoef<T>& q
     // arithmetic, so the workgroup waits on memory once.
     constexpr int Z = PRE;
     TU up[Z + 2][R + 1][3];
-    T wp[Z + 2][FIRST ? R + 1 : 1][3];
+    T wp[Z + 2][FIRST ? R + 1 : 1];
     T Ep[Z + 2][R];
     int mp[Z + 2][R + 1], mo[Z][R];
-    T fo[Z][R][3], wo[Z][R][3];
+    T fo[Z][R][3], wo[Z][R];
 #pragma unroll
     for (int t = 0; t < Z + 2; ++t) load_plane(kc0 - 1 + t, up[t], wp[t], mp[t]);
 #pragma unroll
@@ -556,7 +561,7 @@ __device__ __forceinline__ void stream_tile(const Level& L, const HaarCoef<T>& q
         load_plane(kk + 1, uB, wB, mB);
         load_layer(kk, EB);
         int mo[R];
-        T fo[R][3], wo[R][3];
+        T fo[R][3], wo[R];
         load_out(kk, mo, fo, wo);
         body(kk, uA, wA, mA, EA, mo, fo, wo, FpA, FpB, TpA, TpB);
       }
@@ -565,7 +570,7 @@ __device__ __forceinline__ void stream_tile(const Level& L, const HaarCoef<T>& q
         load_plane(kk + 2, uA, wA, mA);
         load_layer(kk + 1, EA);
         int mo[R];
-        T fo[R][3], wo[R][3];
+        T fo[R][3], wo[R];
         load_out(kk + 1, mo, fo, wo);
         body(kk + 1, uB, wB, mB, EB, mo, fo, wo, FpB, FpA, TpB, TpA);
       }
