@@ -313,11 +313,12 @@ int hexmg_element_matrix(double nu, double *Ke_host);
  * or HEXMG_KERNEL_GATHER and,
  * for the streaming kernel, the planes per z-chunk and the tile shape index
  * (rows per thread / waves per workgroup; any output pointer may be NULL).
- * With HEXMG_KERNEL_AUTO the choice is made by timing the candidates
- * (node-gather; every streaming shape with 1..64 planes per chunk -- a chunk
- * of one plane requests all its inputs before any arithmetic) on the
- * grid's stream during the first successful hexmg_set_density, separately
- * for K u, the sweep and the residual. */
+ * With HEXMG_KERNEL_AUTO levels of up to 1e5 nodes (times max_nrhs; 4e5 in
+ * binary32) take a streaming shape by their size; on larger ones the choice is
+ * made by timing the candidates (node-gather; every streaming shape with 1..128
+ * planes per chunk -- a chunk of one plane requests all its inputs before any
+ * arithmetic) with max_nrhs right-hand sides on the grid's stream during the first
+ * successful hexmg_set_density, separately for K u, the sweep and the residual. */
 int hexmg_kernel_choice(hexmg_grid_t grid, int level, int dtype, int mode, int *kernel, int *zchunk, int *shape);
 
 /* Overrides the element-product kernel of `level` for dtype (all three

@@ -11,37 +11,65 @@
 
 namespace hexmg {
 
+// What is common to the launches a batch may combine, beside their task type.
+struct BatchParams {
+  int mode = 0, shape = 0;
+  bool pre = false, dot = false;
+  const void* q = nullptr;  // HaarCoef of the grid (of every grid of the class)
+};
+
 // Launches of several grids recorded during hexmg_batch_solve.  Each record
 // holds its grid, its place in that grid's PCG iteration (stage: a stage not
 // above the grid's previous one starts the grid's next chunk, i.e. its next
-// iteration) and its single launch; a launch of a batchable kernel also holds
-// its task and a signature (kernel and template arguments).  flush() launches
-// everything in (chunk, stage) order: each grid's own launches keep their
-// order, and the records of one (chunk, stage) and signature from several grids
-// go out as one launch over all of them.
+// iteration) and either a single launch (one) or, for a batchable kernel, its task
+// and a signature (kernel and template arguments).  flush() launches everything
+// in (chunk, stage) order: each grid's own launches keep their order, and the
+// records of one (chunk, stage) and signature from several grids go out as one
+// launch over all of them.  A batch records about 20 launches per grid and
+// iteration while the GPU runs the previous one, so a task record takes no
+// allocation, and the grids of a flush share one event.
 struct BatchRecorder {
+  static constexpr size_t kTaskBytes = 176;
   struct Rec {
     int grid = 0, chunk = 0, stage = 0, blocks = 0;
     unsigned long long sig = 0;  // 0: launched on its own
+    hipError_t (*group)(const Rec* const*, size_t, hipStream_t) = nullptr;
+    void (*many)() = nullptr;  // the batched launcher, cast back by group
+    BatchParams par;
+    alignas(16) unsigned char task[kTaskBytes];
     std::function<hipError_t(hipStream_t)> one;
-    std::function<hipError_t(const std::vector<const Rec*>&, hipStream_t)> group;
-    std::vector<unsigned char> task;
   };
   std::vector<Rec> recs;
+  std::vector<const Rec*> order;
   std::vector<int> last, chunk;
+  static constexpr int kEvents = 8;  // flushes a run may wait for: the last two, and those of the start
+  hipEvent_t ev[kEvents] = {};
+  int flushes = 0;                    // flushes so far; the records being taken belong to this one
   size_t launches = 0, records = 0;  // launches issued / records taken (statistics)
-  explicit BatchRecorder(int ngrids) : last(ngrids, -1), chunk(ngrids, 0) {}
-  void add(int grid, int stage, Rec r) {
+  explicit BatchRecorder(int ngrids) : last(ngrids, -1), chunk(ngrids, 0) { recs.reserve(64 * ngrids); }
+  ~BatchRecorder() {
+    for (hipEvent_t e : ev)
+      if (e) (void)hipEventDestroy(e);
+  }
+  hipError_t init() {
+    for (hipEvent_t& e : ev) {
+      const hipError_t r = hipEventCreateWithFlags(&e, hipEventDisableTiming);
+      if (r != hipSuccess) return r;
+    }
+    return hipSuccess;
+  }
+  Rec& add(int grid, int stage) {
     if (stage <= last[grid]) ++chunk[grid];
     last[grid] = stage;
+    recs.emplace_back();
+    Rec& r = recs.back();
     r.grid = grid;
     r.chunk = chunk[grid];
     r.stage = stage;
-    recs.push_back(std::move(r));
+    return r;
   }
   hipError_t flush(hipStream_t s) {
-    std::vector<const Rec*> order;
-    order.reserve(recs.size());
+    order.clear();
     for (const Rec& r : recs) order.push_back(&r);
     std::stable_sort(order.begin(), order.end(), [](const Rec* a, const Rec* b) {
       if (a->chunk != b->chunk) return a->chunk < b->chunk;
@@ -57,17 +85,14 @@ struct BatchRecorder {
         while (j < order.size() && order[j]->chunk == a->chunk && order[j]->stage == a->stage &&
                order[j]->sig == a->sig)
           ++j;
-      hipError_t e = hipSuccess;
-      if (j - i == 1) {
-        e = a->one(s);
-      } else {
-        std::vector<const Rec*> grp(order.begin() + i, order.begin() + j);
-        e = a->group(grp, s);
-      }
+      const hipError_t e = a->sig ? a->group(&order[i], j - i, s) : a->one(s);
       ++launches;
       if (e != hipSuccess && err == hipSuccess) err = e;
       i = j;
     }
+    const hipError_t e = hipEventRecord(ev[flushes % kEvents], s);
+    if (e != hipSuccess && err == hipSuccess) err = e;
+    ++flushes;
     records += recs.size();
     recs.clear();
     std::fill(last.begin(), last.end(), -1);
@@ -112,57 +137,54 @@ void emit_launch(hexmg_grid* g, int stage, hipStream_t s, F fn) {
     fn(s);
     return;
   }
-  BatchRecorder::Rec r;
-  r.one = [fn](hipStream_t st) {
+  g->rec->add(g->rec_grid, stage).one = [fn](hipStream_t st) {
     fn(st);
     return hipGetLastError();
   };
-  g->rec->add(g->rec_grid, stage, std::move(r));
 }
 // A runtime call returning its status (event records, copies): now, or recorded.
 template <typename F>
 hipError_t emit_api(hexmg_grid* g, int stage, hipStream_t s, F fn) {
   if (!g->rec) return fn(s);
-  BatchRecorder::Rec r;
-  r.one = fn;
-  g->rec->add(g->rec_grid, stage, std::move(r));
+  g->rec->add(g->rec_grid, stage).one = fn;
   return hipSuccess;
 }
 // A launch of a batchable kernel: task A with `blocks` workgroups; sig
 // identifies kernel and template arguments; one(stream) is its single launch,
-// many(batch, stream) launches a Batch<A>.
-template <typename A, typename One, typename Many>
+// many(batch, par, stream) launches a Batch<A>.
+template <typename A>
+using ManyFn = void (*)(const Batch<A>&, const BatchParams&, hipStream_t);
+template <typename A>
+hipError_t launch_group(const BatchRecorder::Rec* const* rs, size_t n, hipStream_t st) {
+  for (size_t i = 0; i < n; i += kMaxBatch) {
+    Batch<A> b;
+    b.n = (int)std::min<size_t>(kMaxBatch, n - i);
+    b.begin[0] = 0;
+    for (int t = 0; t < b.n; ++t) {
+      std::memcpy((void*)&b.a[t], rs[i + t]->task, sizeof(A));
+      b.begin[t + 1] = b.begin[t] + rs[i + t]->blocks;
+    }
+    reinterpret_cast<ManyFn<A>>(rs[i]->many)(b, rs[i]->par, st);
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+  }
+  return hipSuccess;
+}
+template <typename A, typename One>
 void emit_task(hexmg_grid* g, int stage, hipStream_t s, unsigned long long sig, const A& task, int blocks, One one,
-               Many many) {
+               ManyFn<A> many, const BatchParams& par = {}) {
+  static_assert(sizeof(A) <= BatchRecorder::kTaskBytes, "task too large for a record");
   if (!g->rec) {
     one(s);
     return;
   }
-  BatchRecorder::Rec r;
+  BatchRecorder::Rec& r = g->rec->add(g->rec_grid, stage);
   r.sig = sig;
   r.blocks = blocks;
-  r.task.resize(sizeof(A));
-  std::memcpy(r.task.data(), &task, sizeof(A));
-  r.one = [one](hipStream_t st) {
-    one(st);
-    return hipGetLastError();
-  };
-  r.group = [many](const std::vector<const BatchRecorder::Rec*>& rs, hipStream_t st) {
-    for (size_t i = 0; i < rs.size(); i += kMaxBatch) {
-      Batch<A> b;
-      b.n = (int)std::min<size_t>(kMaxBatch, rs.size() - i);
-      b.begin[0] = 0;
-      for (int t = 0; t < b.n; ++t) {
-        std::memcpy(&b.a[t], rs[i + t]->task.data(), sizeof(A));
-        b.begin[t + 1] = b.begin[t] + rs[i + t]->blocks;
-      }
-      many(b, st);
-      const hipError_t e = hipGetLastError();
-      if (e != hipSuccess) return e;
-    }
-    return hipSuccess;
-  };
-  g->rec->add(g->rec_grid, stage, std::move(r));
+  std::memcpy(r.task, (const void*)&task, sizeof(A));
+  r.group = launch_group<A>;
+  r.many = reinterpret_cast<void (*)()>(many);
+  r.par = par;
 }
 // signature of a batchable launch: kernel kind, element sizes, mode/shape/flags
 inline unsigned long long batch_sig(int kind, int a = 0, int b = 0, int c = 0, int d = 0, int e = 0) {
@@ -447,7 +469,10 @@ void launch_choice(hexmg_grid* g, const hexmg_grid::Choice& ch, int mode, int le
         [=](hipStream_t st) {
           launch_stream<T>(mode, false, shape, L, q, E, u, f, wd, y, zc, nrhs, act, st, LaunchTimer{}, dotp);
         },
-        [=](const Batch<StreamTask<T>>& b, hipStream_t st) { launch_stream_batch<T>(mode, shape, pre, dot, b, q, st); });
+        [](const Batch<StreamTask<T>>& b, const BatchParams& p, hipStream_t st) {
+          launch_stream_batch<T>(p.mode, p.shape, p.pre, p.dot, b, *static_cast<const HaarCoef<T>*>(p.q), st);
+        },
+        BatchParams{mode, shape, pre, dot, f32 ? (const void*)&g->hq32 : (const void*)&g->hq64});
     return;
   }
   const hexmg_grid::Choice c = ch;
@@ -456,9 +481,33 @@ void launch_choice(hexmg_grid* g, const hexmg_grid::Choice& ch, int mode, int le
   });
 }
 
+// Choice by size alone, for levels on which a launch is mostly its own latency: one
+// plane per chunk (every input requested at once) and the least work per thread.
+// Timed back to back, a binary32 (binary64) product takes 3.4 (3.9) us with one row
+// per thread, whatever the size up to 4e4 nodes, and the tile of two rows is the
+// faster one from 1e5 to 4e5 (7.1 against 8.0 us at 2.8e5); in binary64 the timed
+// choice varies there.  The differences between the other candidates are within
+// the noise of timing such launches, and grids that share a choice share their
+// batched launches.  Right-hand sides count as nodes (they are more workgroups of one launch).
+bool choice_by_size(const Level& L, bool f32, int max_nrhs, hexmg_grid::Choice* c) {
+  const long long n = (long long)L.nn * max_nrhs;
+  if ((long long)L.nzn * max_nrhs > 65535) return false;  // launch grid limit
+  if (n <= 100000) {
+    *c = {HEXMG_KERNEL_STREAM, 1, f32 ? 6 : 2};
+    return true;
+  }
+  if (f32 && n <= 400000) {
+    *c = {HEXMG_KERNEL_STREAM, 1, 0};
+    return true;
+  }
+  return false;
+}
+
 // Times the candidate kernels of one level in one precision in each of the
 // three modes (K u, damped-Jacobi sweep, residual; zero vectors, the level's
-// own scratch buffers) and keeps the fastest per mode.  The streaming kernel
+// own scratch buffers, as many right-hand sides as the grid is made for: eight at
+// 97x49x49 nodes take other tiles than one) and keeps the fastest per mode;
+// levels small enough take choice_by_size instead.  The streaming kernel
 // is kept unless the node-gather is more than 5% faster.
 // modes: how many of the three modes to time (1 = K u only; f and wd may then
 // be null).
@@ -466,25 +515,31 @@ template <typename T>
 int tune_level(hexmg_grid* g, int level, T* u, T* f, T* y, const T* wd, std::array<hexmg_grid::Choice, 3>* out,
                hipStream_t s, int modes = 3) {
   const Level& L = g->lv[level];
-  const size_t bytes = 3ull * L.nn * sizeof(T);
+  const bool f32 = sizeof(T) == 4;
+  // no more right-hand sides than fill the chip several times over
+  const int nrhs = (int)std::min<long long>(g->desc.max_nrhs, (1500000 + L.nn - 1) / L.nn);
+  if (hexmg_grid::Choice c; choice_by_size(L, f32, g->desc.max_nrhs, &c)) {
+    for (int mode = 0; mode < modes; ++mode) (*out)[mode] = c;
+    return 0;
+  }
+  const size_t bytes = 3ull * L.nn * nrhs * sizeof(T);
   HIP_TRY(hipMemsetAsync(u, 0, bytes, s));
   if (f) HIP_TRY(hipMemsetAsync(f, 0, bytes, s));
-  const bool f32 = sizeof(T) == 4;
   // the mixed form's binary64 K p reads the binary32 direction: its own kernels are timed
   const bool u32in = !f32 && modes == 1 && g->desc.precision == HEXMG_MIXED;
-  if (u32in) HIP_TRY(hipMemsetAsync(g->p32, 0, 3ull * L.nn * sizeof(float), s));
+  if (u32in) HIP_TRY(hipMemsetAsync(g->p32, 0, 3ull * L.nn * nrhs * sizeof(float), s));
   auto run = [&](const hexmg_grid::Choice& c, int mode) {
     if constexpr (sizeof(T) == 8) {
       if (u32in) {
         const HaarCoef<double> q = *reinterpret_cast<const HaarCoef<double>*>(&g->hq64);
         if (c.kernel == HEXMG_KERNEL_STREAM)
-          launch_apply_u32(c.shape, L, q, g->E64[level], g->p32, y, c.zchunk, 1, nullptr, s);
+          launch_apply_u32(c.shape, L, q, g->E64[level], g->p32, y, c.zchunk, nrhs, nullptr, s);
         else
-          launch_gather_apply_u32(L, g->Ke64, g->E64[level], g->p32, y, 1, nullptr, s);
+          launch_gather_apply_u32(L, g->Ke64, g->E64[level], g->p32, y, nrhs, nullptr, s);
         return;
       }
     }
-    launch_choice<T>(g, c, mode, level, u, f, wd, y, 1, s);
+    launch_choice<T>(g, c, mode, level, u, f, wd, y, nrhs, s);
   };
   std::vector<hexmg_grid::Choice> cand;
   for (int sh = 0; sh < stream_shapes(f32); ++sh)
@@ -498,17 +553,21 @@ int tune_level(hexmg_grid* g, int level, T* u, T* f, T* y, const T* wd, std::arr
   for (int mode = 0; mode < modes; ++mode) {
     float best_stream = 1e30f, best_gather = 1e30f;
     hexmg_grid::Choice bs{HEXMG_KERNEL_STREAM, 4, 0};
-    // small levels run for a few microseconds per launch: more repetitions
-    // keep the timer's noise below the differences between candidates
-    const int reps = L.ne < 100000 ? 12 : 3;
+    const int reps = (long long)L.nn * nrhs < 400000 ? 12 : 3;
     for (const auto& c : cand) {
-      run(c, mode);
-      HIP_TRY(hipEventRecord(e0, s));
-      for (int rep = 0; rep < reps; ++rep) run(c, mode);
-      HIP_TRY(hipEventRecord(e1, s));
-      HIP_TRY(hipEventSynchronize(e1));
       float ms = 0.f;
-      HIP_TRY(hipEventElapsedTime(&ms, e0, e1));
+      auto timed = [&](int n) -> int {
+        HIP_TRY(hipEventRecord(e0, s));
+        for (int rep = 0; rep < n; ++rep) run(c, mode);
+        HIP_TRY(hipEventRecord(e1, s));
+        HIP_TRY(hipEventSynchronize(e1));
+        HIP_TRY(hipEventElapsedTime(&ms, e0, e1));
+        return 0;
+      };
+      // the first launch (cold, so up to half as long again) rules most candidates out
+      if (int e = timed(1)) return e;
+      if (ms * reps > 1.6f * std::min(best_stream, best_gather)) continue;
+      if (int e = timed(reps)) return e;
       if (c.kernel == HEXMG_KERNEL_GATHER) {
         best_gather = ms;
       } else if (ms < best_stream) {
@@ -587,9 +646,11 @@ void apply_p32(hexmg_grid* g, const float* u, double* y, int nrhs, hipStream_t s
           batch_sig(kBkStreamU32, sizeof(double), kApply, shape, pre, dot) | ((unsigned long long)g->rec_class << 48),
           task, task.gx * task.gy * task.nchunks * nrhs,
           [=](hipStream_t st) { launch_apply_u32(shape, L, q, E, u, y, zc, nrhs, act, st, LaunchTimer{}, dotp); },
-          [=](const Batch<StreamTask<double>>& b, hipStream_t st) {
-            launch_stream_batch<double>(kApply, shape, pre, dot, b, q, st, true);
-          });
+          [](const Batch<StreamTask<double>>& b, const BatchParams& p, hipStream_t st) {
+            launch_stream_batch<double>(p.mode, p.shape, p.pre, p.dot, b, *static_cast<const HaarCoef<double>*>(p.q),
+                                        st, true);
+          },
+          BatchParams{kApply, shape, pre, dot, &g->hq64});
     } else {
       emit_launch(g, g->stage, s,
                   [=](hipStream_t st) { launch_gather_apply_u32(L, Ke, E, u, y, nrhs, act, st, LaunchTimer{}); });
@@ -727,7 +788,7 @@ void vcycle_level(hexmg_grid* g, VView<T>& v, int l, const T* f, T* out, int nrh
     emit_task<GemvTask<T>>(
         g, kStCoarse, s, batch_sig(kBkGemv, sizeof(T)), task, task.gx * nrhs,
         [=](hipStream_t st) { launch_coarse_gemv<T>(nc, Ainv, f, out, nrhs, act, st); },
-        [](const Batch<GemvTask<T>>& b, hipStream_t st) { launch_coarse_gemv_batch<T>(b, st); });
+        [](const Batch<GemvTask<T>>& b, const BatchParams&, hipStream_t st) { launch_coarse_gemv_batch<T>(b, st); });
     return;
   }
   const int nu = g->desc.smooth_sweeps;
@@ -755,11 +816,11 @@ void vcycle_level(hexmg_grid* g, VView<T>& v, int l, const T* f, T* out, int nrh
   {
     const Level F = L, C = g->lv[l + 1];
     RestrictTask<T> task{F, C, v.r[l], v.f[l + 1], act, fuse ? v.wd[l + 1] : nullptr, fuse ? v.t[l + 1] : nullptr,
-                         restrict_blocks(C)};
+                         restrict_blocks(C), restrict_slab(C)};
     emit_task<RestrictTask<T>>(
         g, st_down(l, 95), s, batch_sig(kBkRestrict, sizeof(T)), task, task.gx * nrhs,
         [=](hipStream_t st) { launch_restrict<T>(F, C, task.r, task.fc, nrhs, act, st, task.wdc, task.tc); },
-        [](const Batch<RestrictTask<T>>& b, hipStream_t st) { launch_restrict_batch<T>(b, st); });
+        [](const Batch<RestrictTask<T>>& b, const BatchParams&, hipStream_t st) { launch_restrict_batch<T>(b, st); });
   }
   int& tail = sizeof(T) == 4 ? g->tail32 : g->tail64;
   const int blocks = sizeof(T) == 4 ? g->tail_blocks32 : g->tail_blocks64;
@@ -775,11 +836,11 @@ void vcycle_level(hexmg_grid* g, VView<T>& v, int l, const T* f, T* out, int nrh
   if (!done) vcycle_level<T>(g, v, l + 1, v.f[l + 1], v.u[l + 1], nrhs, act, s, fuse);
   {
     const Level F = L, C = g->lv[l + 1];
-    ProlongTask<T> task{F, C, v.u[l + 1], buf[cur], act, prolong_blocks(F)};
+    ProlongTask<T> task{F, C, v.u[l + 1], buf[cur], act, prolong_blocks(F), prolong_slab(F)};
     emit_task<ProlongTask<T>>(
         g, st_up(l, 0), s, batch_sig(kBkProlong, sizeof(T)), task, task.gx * nrhs,
         [=](hipStream_t st) { launch_prolong_add<T>(F, C, task.ec, task.u, nrhs, act, st); },
-        [](const Batch<ProlongTask<T>>& b, hipStream_t st) { launch_prolong_add_batch<T>(b, st); });
+        [](const Batch<ProlongTask<T>>& b, const BatchParams&, hipStream_t st) { launch_prolong_add_batch<T>(b, st); });
   }
   for (int it = 0; it < nu; ++it) {
     g->stage = st_up(l, 1 + it);
@@ -1010,8 +1071,14 @@ int hexmg_grid_create(const hexmg_grid_desc* d, void* workspace, size_t bytes, v
         g->choice64[l][m] = {HEXMG_KERNEL_GATHER, 0, 0};
         g->choice32[l][m] = {HEXMG_KERNEL_GATHER, 0, 0};
       } else {
+        // (kept where nothing is timed: HEXMG_KERNEL_STREAM, and K u in a precision whose
+        // V-cycle vectors the grid does not hold)
         g->choice64[l][m] = {HEXMG_KERNEL_STREAM, stream_zchunk(g->lv[l], false, 1), 1};
         g->choice32[l][m] = {HEXMG_KERNEL_STREAM, stream_zchunk(g->lv[l], true, 1), 1};
+        if (d->kernel == HEXMG_KERNEL_AUTO) {
+          choice_by_size(g->lv[l], false, d->max_nrhs, &g->choice64[l][m]);
+          choice_by_size(g->lv[l], true, d->max_nrhs, &g->choice32[l][m]);
+        }
       }
     }
   }
@@ -1260,6 +1327,7 @@ struct PcgRun {
   hipStream_t s = nullptr;
   hexmg_solve_info* info = nullptr;
   hipEvent_t ev[3] = {nullptr, nullptr, nullptr}, t0 = nullptr, t1 = nullptr;
+  int slot_flush[3] = {0, 0, 0};
   enum Phase { kIterate, kFinish, kDone } phase = kIterate;
   int issued = 0, target = 0, final_slot = 0, status = 0;
   int limit = 0;    // host iteration number the run may not pass (maxit, moved by restarts)
@@ -1286,7 +1354,11 @@ struct PcgRun {
   }
   long long N() const { return 3ll * g->lv[0].nn; }
   double* slot(int k) const { return g->host_ring + (size_t)(k % 3) * kScalars * g->desc.max_nrhs; }
-  hipEvent_t wait_event() const { return ev[(phase == kFinish ? final_slot : target) % 3]; }
+  // (batched: the event of the flush that holds the slot's last launch)
+  hipEvent_t wait_event() const {
+    const int k = (phase == kFinish ? final_slot : target) % 3;
+    return g->rec ? g->rec->ev[slot_flush[k] % BatchRecorder::kEvents] : ev[k];
+  }
   // the scalars of slot k reach the host by a copy (final phase) or, for a CG
   // iteration, written by the iteration's last kernel itself
   int post(int k, bool copy, int stage) {
@@ -1298,8 +1370,10 @@ struct PcgRun {
         return hipMemcpyAsync(dst, src, bytes, hipMemcpyDeviceToHost, st);
       }));
     }
-    hipEvent_t e = ev[k % 3];
-    HIP_TRY(emit_api(g, stage + 1, s, [=](hipStream_t st) { return hipEventRecord(e, st); }));
+    if (g->rec)
+      slot_flush[k % 3] = g->rec->flushes;
+    else
+      HIP_TRY(hipEventRecord(ev[k % 3], s));
     return 0;
   }
   // iteration k (1-based): q = A p, alpha, the r update (its x update follows
@@ -1391,7 +1465,7 @@ struct PcgRun {
       emit_task<RrCheckTask>(
           g, kStEnd + 400, s, batch_sig(kBkRrCheck), task, nb,
           [=](hipStream_t st) { launch_rr_check(task.rr_partials, task.sc, task.active, task.host_slot, b, st); },
-          [](const Batch<RrCheckTask>& bt, hipStream_t st) { launch_rr_check_batch(bt, st); });
+          [](const Batch<RrCheckTask>& bt, const BatchParams&, hipStream_t st) { launch_rr_check_batch(bt, st); });
     }
     issued = k;
     return post(k, false, kStEnd + 500);
@@ -1409,7 +1483,7 @@ struct PcgRun {
                                         task.rr_partials, task.parity, task.wdinv, task.f32, task.t, b, st,
                                         task.repl);
         },
-        [](const Batch<UpdateRTask<TW, TQ>>& bt, hipStream_t st) { launch_update_r_first_batch<TW, TQ>(bt, st); });
+        [](const Batch<UpdateRTask<TW, TQ>>& bt, const BatchParams&, hipStream_t st) { launch_update_r_first_batch<TW, TQ>(bt, st); });
   }
   template <typename TZ>
   void emit_update_px(int nrz, int parity, const TZ* z, float* p32) {
@@ -1421,7 +1495,7 @@ struct PcgRun {
           launch_update_px<TZ>(task.n, task.rz_partials, task.nrz, task.sc, task.active, task.z, task.p, task.x,
                                task.parity, b, st, task.p32, task.p32b);
         },
-        [](const Batch<UpdatePxTask<TZ>>& bt, hipStream_t st) { launch_update_px_batch<TZ>(bt, st); });
+        [](const Batch<UpdatePxTask<TZ>>& bt, const BatchParams&, hipStream_t st) { launch_update_px_batch<TZ>(bt, st); });
   }
   // z = M^{-1} r (its first sweep already formed), beta, x += alpha p (iteration k)
   // and p = z + beta p, then iteration k+1
@@ -1765,6 +1839,7 @@ int hexmg_batch_solve(hexmg_grid_t* grids, int ngrids, const double* const* f, d
     e = r.init();
   }
   BatchRecorder rec(ngrids);
+  if (!e && rec.init() != hipSuccess) e = fail(HEXMG_ERR_DEVICE, "event creation failed");
   if (!e) e = drive_batched(runs, rec, s);
   for (auto& r : runs) worst = combine_status(worst, r.status);
   if (!e) (void)hipStreamSynchronize(s);

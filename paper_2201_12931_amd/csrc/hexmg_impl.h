@@ -135,10 +135,12 @@ __device__ inline int xcd_band_index(int l, int T, long long first) {
 // the grid, the blocks that read the same rows of the other level run on one
 // L2, and the next slab's band (the next plane) re-reads rows the same L2 has
 // just held.
-__device__ inline int xcd_band_block(int slab) {
-  const int n = (int)gridDim.x, b = (int)blockIdx.x;
+__device__ inline int xcd_band_of(int b, int n, int slab, long long first) {  // block b of n, block 0 with id `first`
   const int s0 = b - b % slab;
-  return s0 + xcd_band_index(b - s0, min(slab, n - s0), (long long)n * blockIdx.y + s0);
+  return s0 + xcd_band_index(b - s0, min(slab, n - s0), first + s0);
+}
+__device__ inline int xcd_band_block(int slab) {
+  return xcd_band_of(blockIdx.x, gridDim.x, slab, (long long)gridDim.x * blockIdx.y);
 }
 // A slab of about one plane of `per_plane` blocks, a multiple of 8.
 inline int band_slab(long long per_plane) { return (int)per_plane > 8 ? (per_plane + 7) / 8 * 8 : 8; }
@@ -175,7 +177,7 @@ struct RestrictTask {
   const int* act;
   const T* wdc;
   T* tc;
-  int gx;
+  int gx, slab;
 };
 template <typename T>
 struct ProlongTask {
@@ -183,7 +185,7 @@ struct ProlongTask {
   const T* ec;
   T* u;
   const int* act;
-  int gx;
+  int gx, slab;
 };
 template <typename T>
 struct GemvTask {
@@ -244,7 +246,10 @@ static_assert(sizeof(Batch<StreamTask<double>>) <= 4096, "stream task table too 
 static_assert(sizeof(Batch<RestrictTask<double>>) <= 4096, "restriction task table too large for kernel arguments");
 static_assert(sizeof(Batch<UpdateRTask<double, double>>) <= 4096, "update task table too large for kernel arguments");
 // workgroups per right-hand side of the single launches
+// and (transfers) the slabs of their banded order
 int restrict_blocks(const Level& C);
+int restrict_slab(const Level& C);
+int prolong_slab(const Level& F);
 int prolong_blocks(const Level& F);
 int gemv_blocks(int n);
 // most partials a fused dot product may leave per right-hand side

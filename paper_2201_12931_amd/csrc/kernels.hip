@@ -129,7 +129,9 @@ __global__ void k_restrict_batch(Batch<RestrictTask<T>> tb) {
   const int t = batch_task(tb.begin, tb.n, (int)blockIdx.x);
   const RestrictTask<T>& a = tb.a[t];
   const int local = (int)blockIdx.x - tb.begin[t];
-  restrict_block<T>(a.F, a.C, a.r, a.fc, a.act, a.wdc, a.tc, local % a.gx, local / a.gx);
+  const int bx = local % a.gx;
+  restrict_block<T>(a.F, a.C, a.r, a.fc, a.act, a.wdc, a.tc,
+                    xcd_band_of(bx, a.gx, a.slab, (long long)blockIdx.x - bx), local / a.gx);
 }
 
 // Fine correction u += M P e_c by rows: each wave takes 64 consecutive nodes of
@@ -212,7 +214,9 @@ __global__ void k_prolong_add_batch(Batch<ProlongTask<T>> tb) {
   const int t = batch_task(tb.begin, tb.n, (int)blockIdx.x);
   const ProlongTask<T>& a = tb.a[t];
   const int local = (int)blockIdx.x - tb.begin[t];
-  prolong_block<T>(a.F, a.C, a.ec, a.u, a.act, local % a.gx, local / a.gx);
+  const int bx = local % a.gx;
+  prolong_block<T>(a.F, a.C, a.ec, a.u, a.act, xcd_band_of(bx, a.gx, a.slab, (long long)blockIdx.x - bx),
+                   local / a.gx);
 }
 
 // ---------------------------------------------------------------------------
@@ -972,8 +976,7 @@ void launch_jacobi_first_from64(long long n, const float* wdinv, const double* r
 template <typename T>
 void launch_restrict(const Level& F, const Level& C, const T* r, T* fc, int nrhs, const int* act, hipStream_t s,
                      const T* wdc, T* tc) {
-  // a slab: the blocks of one coarse plane
-  const int slab = band_slab(((long long)C.nxn * C.nyn + kBlock - 1) / kBlock);
+  const int slab = restrict_slab(C);
   k_restrict<T><<<dim3(blocks_for(C.nn), nrhs), kBlock, 0, s>>>(F, C, r, fc, act, wdc, tc, slab);
 }
 template void launch_restrict<double>(const Level&, const Level&, const double*, double*, int, const int*,
@@ -984,8 +987,7 @@ template void launch_restrict<float>(const Level&, const Level&, const float*, f
 template <typename T>
 void launch_prolong_add(const Level& F, const Level& C, const T* ec, T* u, int nrhs, const int* act,
                         hipStream_t s) {
-  // a slab: the blocks of the row quads of one pair of fine planes
-  const int slab = band_slab((long long)((F.nxn + 63) / 64) * ((((F.nyn + 1) / 2) + 3) / 4));
+  const int slab = prolong_slab(F);
   k_prolong_add<T><<<dim3(prolong_blocks(F), nrhs), kBlock, 0, s>>>(F, C, ec, u, act, slab);
 }
 template void launch_prolong_add<double>(const Level&, const Level&, const double*, double*, int, const int*,
@@ -1125,6 +1127,11 @@ void launch_f64_to_f32(long long n, const double* a, float* b, int nrhs, const i
 // ---------------------------------------------------------------------------
 // Batched launches (several grids; see Batch in hexmg_impl.h).
 int restrict_blocks(const Level& C) { return blocks_for(C.nn); }
+// the blocks of one coarse plane; of the row quads of one pair of fine planes
+int restrict_slab(const Level& C) { return band_slab(((long long)C.nxn * C.nyn + kBlock - 1) / kBlock); }
+int prolong_slab(const Level& F) {
+  return band_slab((long long)((F.nxn + 63) / 64) * ((((F.nyn + 1) / 2) + 3) / 4));
+}
 int prolong_blocks(const Level& F) {
   return ((F.nxn + 63) / 64) * ((((F.nyn + 1) / 2) * ((F.nzn + 1) / 2) + 3) / 4);
 }
