@@ -613,10 +613,10 @@ void gather(hexmg_grid* g, int mode, int level, const T* u, const T* f, const T*
   }
   LaunchTimer t;
   if (a && b) t = LaunchTimer{a, b};
-  const int cm = mode == kSmoothFirst ? kSmooth : mode;  // the sweep's kernel choice
+  const int cm = mode == kSmoothFirst ? kSmooth : (mode == kFinal ? kApply : mode);  // whose kernel choice it takes
   launch_choice<T>(g, (f32 ? g->choice32[level] : g->choice64[level])[cm], mode, level, u, f, wd, y, nrhs, s, maskin,
                    act, t, dotp);
-  if (a && b) g->recs.push_back({family_of(mode, f32), a, b, g->prof_tag});
+  if (a && b) g->recs.push_back({family_of(mode == kFinal ? kApply : mode, f32), a, b, g->prof_tag});
 }
 
 // y = A u at level 0 in binary64 on u, a binary32 search direction of the
@@ -945,53 +945,33 @@ int tune_tail(hexmg_grid* g, hipStream_t s) {
 
 // z = M^{-1} r (the V-cycle in the grid's precision) for nrhs <= max_nrhs
 // binary64 right-hand sides, and the partials of r . z; returns how many
-// partials each right-hand side has (kReduceBlocks apart from fuse_dot).  In
-// mixed precision the binary32 right-hand side is formed inside the first
-// sweep, and z is written in binary64 only with write_z; otherwise it stays in
-// the binary32 buffer g->vu32[0] (the CG update widens it on the fly).  With
-// first_done the first sweep (and in mixed precision the binary32 copy of r)
-// was already written by the CG residual update.  With fuse_dot the partials
-// come from the last level-0 sweep where it can form them (in mixed precision
-// as the binary32 copy of r, which the V-cycle consumes, times z), the
-// returned count apart.
-int precondition(hexmg_grid* g, const double* r, double* z, double* rz_partials, int nrhs, const int* act,
-                 hipStream_t s, bool write_z = true, bool first_done = false, bool fuse_dot = false) {
+// partials each right-hand side has (kReduceBlocks apart from fuse_dot).  What
+// formed r also wrote the first sweep where it is stored, and in mixed precision
+// the binary32 copy of r, which the V-cycle consumes.  In mixed precision z is
+// written in binary64 only with z non-null; otherwise it stays in the binary32 buffer
+// z32 (the CG update widens it on the fly).  With fuse_dot the partials come from
+// the last level-0 sweep where it can form them (in mixed precision as the
+// binary32 copy of r times z), the returned count apart.
+int precondition(hexmg_grid* g, const double* r, double* z, float* z32, double* rz_partials, int nrhs, const int* act,
+                 hipStream_t s, bool fuse_dot) {
   const long long N = 3ll * g->lv[0].nn;
   if (g->desc.precision == HEXMG_FP64) {
     VView<double> v = view64(g);
     const int nd = fuse_dot ? sweep_dot_parts<double>(g) : 0;
-    vcycle_level<double>(g, v, 0, r, z, nrhs, act, s, first_done, false,
-                         nd ? parts_target(g, nd, rz_partials) : nullptr);
+    vcycle_level<double>(g, v, 0, r, z, nrhs, act, s, true, false, nd ? parts_target(g, nd, rz_partials) : nullptr);
     if (nd) return sum_big(g, nd, rz_partials, nrhs, act, kStEnd, s);
     emit_launch(g, kStEnd, s, [=](hipStream_t st) { launch_dot_partial(N, r, z, rz_partials, nrhs, act, st); });
     return kReduceBlocks;
   }
   VView<float> v = view32(g);
-  const int nd = fuse_dot && !write_z ? sweep_dot_parts<float>(g) : 0;
-  float* f32 = g->vf32[0];
-  float* u32 = g->vu32[0];
-  if (g->L == 1) {  // the coarsest level is the whole grid: no sweep to fuse into
-    if (!first_done)
-      emit_launch(g, st_down(0, 0), s, [=](hipStream_t st) { launch_f64_to_f32(N, r, f32, nrhs, act, st); });
-    vcycle_level<float>(g, v, 0, f32, u32, nrhs, act, s);
-  } else {
-    if (!first_done) {
-      const float* wd = g->wd32[0];
-      float* t32 = g->vt32[0];
-      if (first_fused<float>(g))  // the second sweep forms the first: only the binary32 copy of r
-        emit_launch(g, st_down(0, 0), s, [=](hipStream_t st) { launch_f64_to_f32(N, r, f32, nrhs, act, st); });
-      else
-        emit_launch(g, st_down(0, 0), s,
-                    [=](hipStream_t st) { launch_jacobi_first_from64(N, wd, r, f32, t32, nrhs, act, st); });
-    }
-    vcycle_level<float>(g, v, 0, f32, u32, nrhs, act, s, true, false,
-                        nd ? parts_target(g, nd, rz_partials) : nullptr);
-  }
+  const int nd = fuse_dot && !z ? sweep_dot_parts<float>(g) : 0;
+  vcycle_level<float>(g, v, 0, g->vf32[0], z32, nrhs, act, s, true, false,
+                      nd ? parts_target(g, nd, rz_partials) : nullptr);
   if (nd) return sum_big(g, nd, rz_partials, nrhs, act, kStEnd, s);
-  if (write_z)
-    emit_launch(g, kStEnd, s, [=](hipStream_t st) { launch_to64_dot(N, u32, r, z, rz_partials, nrhs, act, st); });
+  if (z)
+    emit_launch(g, kStEnd, s, [=](hipStream_t st) { launch_to64_dot(N, z32, r, z, rz_partials, nrhs, act, st); });
   else
-    emit_launch(g, kStEnd, s, [=](hipStream_t st) { launch_dot_mixed(N, u32, r, rz_partials, nrhs, act, st); });
+    emit_launch(g, kStEnd, s, [=](hipStream_t st) { launch_dot_mixed(N, z32, r, rz_partials, nrhs, act, st); });
   return kReduceBlocks;
 }
 
@@ -1446,7 +1426,7 @@ struct PcgRun {
       if (replace) {
         double* p = g->p;
         double* x = u;
-        emit_launch(g, kStEnd + 310, s, [=](hipStream_t st) { launch_flush_x(n, sc, p, x, b, st, repl); });
+        emit_launch(g, kStEnd + 310, s, [=](hipStream_t st) { launch_flush_x(n, sc, p, x, b, st, repl, nullptr, nullptr, true); });
         g->stage = kStEnd + 320;
         gather<double>(g, kApply, 0, u, nullptr, nullptr, g->q, nb, s, false, g->repl);
         const Level L0 = g->lv[0];
@@ -1503,10 +1483,10 @@ struct PcgRun {
     const int k = issued;
     g->prof_tag = k + 1 - tag_off;
     if (g->desc.precision == HEXMG_FP64) {
-      const int nrz = precondition(g, g->r, g->z, g->partials, nb, g->active, s, true, true, true);
+      const int nrz = precondition(g, g->r, g->z, nullptr, g->partials, nb, g->active, s, true);
       emit_update_px<double>(nrz, (k - 1) & 1, g->z, nullptr);
     } else {
-      const int nrz = precondition(g, g->r, g->z, g->partials, nb, g->active, s, false, true, true);
+      const int nrz = precondition(g, g->r, nullptr, g->vu32[0], g->partials, nb, g->active, s, true);
       emit_update_px<float>(nrz, (k - 1) & 1, g->vu32[0], g->p32);  // mixed: the direction itself
     }
     return issue_iteration(k + 1);
@@ -1528,22 +1508,28 @@ struct PcgRun {
     int* act = g->active;
     const double* ff = f;
     const double rt2 = rtol > 0.0 ? rtol * rtol : -1.0;
-    emit_launch(g, kStStart + 1, s, [=](hipStream_t st) {
-      launch_pcg_start(L0, ff, r, x, parts, b, st);  // r0 = M f, x0 = 0, ||r0||^2 partials
-    });
+    // r0 = M f, ||r0||^2 partials, and the first preconditioner's inputs
+    double* xz = m32() ? x : nullptr;
+    if (g->desc.precision == HEXMG_FP64) {
+      const double* wd = g->wd64[0];
+      double* t = g->L > 1 && !first_fused<double>(g) ? g->vt64[0] : nullptr;
+      emit_launch(g, kStStart + 1, s, [=](hipStream_t st) {
+        launch_pcg_start<double>(L0, ff, r, xz, parts, wd, nullptr, t, b, st);
+      });
+    } else {
+      const float* wd = g->wd32[0];
+      float *f32v = g->vf32[0], *t = g->L > 1 && !first_fused<float>(g) ? g->vt32[0] : nullptr;
+      emit_launch(g, kStStart + 1, s, [=](hipStream_t st) {
+        launch_pcg_start<float>(L0, ff, r, xz, parts, wd, f32v, t, b, st);
+      });
+    }
     emit_launch(g, kStInit, s, [=](hipStream_t st) { launch_pcg_init(rt2, parts, sc, act, b, st); });
     if (maxit == 0) return enqueue_finish(0);
     g->prof_tag = 1;
-    if (p) {
-      precondition(g, g->r, p, g->partials, nb, g->active, s);  // p0 = z0 = M^{-1} r0
-    } else {  // mixed form: z0 stays in the binary32 V-cycle output, which p0 copies
-      precondition(g, g->r, nullptr, g->partials, nb, g->active, s, false);
-      const float* z32 = g->vu32[0];
-      const size_t bytes = (size_t)n * b * sizeof(float);
-      HIP_TRY(emit_api(g, kStEnd + 20, s,
-                       [=](hipStream_t st) { return hipMemcpyAsync(p32, z32, bytes, hipMemcpyDeviceToDevice, st); }));
-    }
-    emit_launch(g, kStEnd + 10, s, [=](hipStream_t st) { launch_reduce_final(parts, sc + kRz0, kScalars, b, st); });
+    // p0 = z0 = M^{-1} r0, written as the direction itself
+    const int nrz = precondition(g, g->r, p, m32() ? g->vu32[0] : p32, g->partials, nb, g->active, s, !m32());
+    emit_launch(g, kStEnd + 10, s,
+                [=](hipStream_t st) { launch_sum_parts(parts, nrz, sc + kRz0, b, act, st, kScalars); });
     if (m32()) emit_launch(g, kStEnd + 20, s, [=](hipStream_t st) { launch_f64_to_f32(n, p, p32, b, act, st); });
     if (int e = issue_iteration(1)) return e;
     if (maxit >= 2)
@@ -1587,7 +1573,7 @@ struct PcgRun {
                   [=](hipStream_t st) { launch_replace_r(L0, ff, q, r, p2, wd, f32v, t32, sc, act, b, st); });
     }
     g->prof_tag = k1 - tag_off;
-    precondition(g, g->r, g->p, g->partials, nb, g->active, s, true, true);  // p = z = M^{-1} r
+    precondition(g, g->r, g->p, g->vu32[0], g->partials, nb, g->active, s, false);  // p = z = M^{-1} r
     double *parts = g->partials, *p = g->p;
     float* p32 = g->p32;
     const int par = (k1 - 1) & 1;
@@ -1610,8 +1596,9 @@ struct PcgRun {
     double *p = g->p, *x = u, *q = g->q, *pa = g->partials, *pb = g->partials2;
     const float *p32 = g->p32, *p32b = g->p32b;
     const double* ff = f;
+    const bool cleared = m32();
     emit_launch(g, kStEnd + 600, s, [=](hipStream_t st) {
-      launch_flush_x(n, sc, p, x, b, st, nullptr, p32, p32b);  // the x updates still pending
+      launch_flush_x(n, sc, p, x, b, st, nullptr, p32, p32b, cleared);  // the x updates still pending
     });
     {
       hipEvent_t e1 = t1;
@@ -1619,10 +1606,19 @@ struct PcgRun {
     }
     g->prof_tag = 0;
     g->stage = kStEnd + 620;
-    gather<double>(g, kApply, 0, u, nullptr, nullptr, g->q, nb, s);  // true residual in binary64
-    emit_launch(g, kStEnd + 630, s, [=](hipStream_t st) {
-      launch_pcg_final(L0, ff, q, x, pa, pb, sc, b, st);  // ||M f - A x||^2, f . x
-    });
+    // ||M f - A x||^2 in binary64 and f . x: from the product's own pass where it is
+    // the streaming kernel and its pairs of partials fit (a restart reads A x, so
+    // HEXMG_MIXED32 keeps it), else A x and a pass over it
+    const hexmg_grid::Choice& ch = g->choice64[0][kApply];
+    const int nbk = ch.kernel == HEXMG_KERNEL_STREAM ? stream_blocks(L0, false, ch.shape, ch.zchunk) : 0;
+    double* pairs = 2 * nbk <= kMaxDotParts ? g->partials : (2 * nbk <= g->big_parts_n ? g->big_parts : nullptr);
+    if (nbk > 0 && pairs && !m32()) {
+      gather<double>(g, kFinal, 0, u, f, nullptr, nullptr, nb, s, false, nullptr, pairs);
+      emit_launch(g, kStEnd + 630, s, [=](hipStream_t st) { launch_pcg_final_pairs(pairs, nbk, sc, b, st); });
+    } else {
+      gather<double>(g, kApply, 0, u, nullptr, nullptr, g->q, nb, s);
+      emit_launch(g, kStEnd + 630, s, [=](hipStream_t st) { launch_pcg_final(L0, ff, q, x, pa, pb, sc, b, st); });
+    }
     final_slot = read + 2;  // a slot no result in flight is written to
     phase = kFinish;
     return post(final_slot, true, kStEnd + 640);

@@ -254,8 +254,9 @@ int prolong_blocks(const Level& F);
 int gemv_blocks(int n);
 // most partials a fused dot product may leave per right-hand side
 constexpr int kMaxDotParts = 8192;  // partials a vector kernel's block sums itself
-// out[r] = sum of parts[r * n .. r * n + n) (fixed order; inactive r skipped)
-void launch_sum_parts(const double* parts, int n, double* out, int nrhs, const int* act, hipStream_t s);
+// out[r * stride] = sum of parts[r * n .. r * n + n) (fixed order; inactive r skipped)
+void launch_sum_parts(const double* parts, int n, double* out, int nrhs, const int* act, hipStream_t s,
+                      int stride = 1);
 
 constexpr int kReduceBlocks = 1024;  // partial sums per reduction (fixed: deterministic)
 constexpr int kOcProbes = 32;       // Lagrange multipliers evaluated per OC pass
@@ -275,13 +276,12 @@ void launch_gather_apply_u32(const Level& L, const double* Ke, const double* E, 
 // mode: 0 y = A u; 1 y = u + wdinv (f - A u); 2 y = f - A u
 // element-product modes; kSmoothFirst (streaming kernel only): a Jacobi sweep
 // whose input is the first sweep from zero, (omega/D) f, formed on load
-enum { kApply = 0, kSmooth = 1, kResidual = 2, kSmoothFirst = 3 };
+// kFinal (streaming kernel, binary64 only): A u is not stored; one pair of partials
+// per workgroup of ||M f - A u||^2 and f . u
+enum { kApply = 0, kSmooth = 1, kResidual = 2, kSmoothFirst = 3, kFinal = 4 };
 
 template <typename T>
 void launch_jacobi_first(const Level& L, const T* wdinv, const T* f, T* u, int nrhs, const int* act, hipStream_t s);
-// binary32 first sweep from a binary64 right-hand side: f32 = (float) r, u = wdinv f32
-void launch_jacobi_first_from64(long long n, const float* wdinv, const double* r, float* f32, float* u, int nrhs,
-                                const int* act, hipStream_t s);
 template <typename T>
 void launch_restrict(const Level& F, const Level& C, const T* r, T* fc, int nrhs, const int* act, hipStream_t s,
                      const T* wdc = nullptr, T* tc = nullptr);
@@ -316,15 +316,20 @@ void launch_dot_partial(long long n, const double* x, const double* y, double* p
 // out[r * stride] = sum of partials[r][0..kReduceBlocks)
 void launch_reduce_final(const double* partials, double* out, int stride, int nrhs, hipStream_t s);
 // CG steps with the scalars computed on the device (see ScalarSlot):
-// start: r = M f, x = 0, partials of ||r||^2 ([nrhs][kReduceBlocks])
-void launch_pcg_start(const Level& L, const double* f, double* r, double* x, double* partials, int nrhs,
-                      hipStream_t s);
+// start: r = M f, partials of ||r||^2 ([nrhs][kReduceBlocks]), the binary32 copy f32
+// of r (TW = float) and the preconditioner's first sweep t (may be null); x_zero
+// (may be null): x to clear
+template <typename TW>
+void launch_pcg_start(const Level& L, const double* f, double* r, double* x_zero, double* partials, const TW* wdinv,
+                      float* f32, TW* t, int nrhs, hipStream_t s);
 // init: ff from the start's partials; active = (ff > 0), its = 0, stop = rtol^2 ff (rtol2 <= 0: never)
 void launch_pcg_init(double rtol2, const double* ff_partials, double* sc, int* active, int nrhs, hipStream_t s);
 // after q = A x: sc[kTmp] = ||M f - q||^2 and sc[kTmp2] = f . x per right-hand
 // side (pa, pb: [nrhs][kReduceBlocks] partials)
 void launch_pcg_final(const Level& L, const double* f, const double* q, const double* x, double* pa, double* pb,
                       double* sc, int nrhs, hipStream_t s);
+// the same from the n pairs of partials per right-hand side of a kFinal launch
+void launch_pcg_final_pairs(const double* parts, int n, double* sc, int nrhs, hipStream_t s);
 // alpha = rz[parity] / (sum of the npq pq partials of a right-hand side, which
 // are also npq apart); r -= alpha q; rr partials; the first Jacobi sweep from
 // zero t = wdinv * r (mixed: on the binary32 copy f32 of r; t may be null);
@@ -359,6 +364,8 @@ void launch_rr_check(const double* rr_partials, double* sc, int* active, double*
 // and in p32b when k is even, and x is brought up to date only after the even
 // iterations, by the two directions then pending (x += alpha_(k-1) p_(k-1),
 // then x += alpha_k p_k, the order and rounding of one update per iteration).
+// The first update of x (after iteration 1, with p null 2; s[kIts]) writes it from
+// zero without reading it, except with p and p32 both given (x cleared at the start).
 template <typename TZ>
 void launch_update_px(long long n, const double* rz_partials, int nrz, double* sc, const int* active, const TZ* z,
                       double* p, double* x, int parity, int nrhs, hipStream_t s, float* p32 = nullptr,
@@ -366,9 +373,11 @@ void launch_update_px(long long n, const double* rz_partials, int nrz, double* s
 // x += alpha p for the right-hand sides where it is still due (s[kXPend]);
 // with p null, the binary32 directions still pending after the right-hand
 // side's last iteration k = s[kIts]: p_k (in p32 for odd k), and for even k
-// also p_(k-1), in the order of launch_update_px
+// also p_(k-1), in the order of launch_update_px.  Unless x was cleared at the start, right-hand
+// sides whose x no update has written yet get it from zero.
 void launch_flush_x(long long n, const double* sc, const double* p, double* x, int nrhs, hipStream_t s,
-                    const int* act = nullptr, const float* p32 = nullptr, const float* p32b = nullptr);
+                    const int* act = nullptr, const float* p32 = nullptr, const float* p32b = nullptr,
+                    bool cleared = false);
 // partials of r . (double) u32 (the binary32 V-cycle output, not widened in memory)
 void launch_dot_mixed(long long n, const float* u32, const double* r, double* partials, int nrhs, const int* act,
                       hipStream_t s);

@@ -96,18 +96,6 @@ __global__ void k_jacobi_first(Level L, const T* __restrict__ wdinv, const T* __
   u[off + i] = (((L.mask[node] >> c) & 1) ? T(L.omega) : wdinv[node]) * f[off + i];
 }
 
-__global__ void k_jacobi_first_from64(long long n, const float* __restrict__ wdinv, const double* __restrict__ r,
-                                      float* __restrict__ f32, float* __restrict__ u, const int* __restrict__ act) {
-  if (act && !act[blockIdx.y]) return;
-  const long long i = (long long)blockIdx.x * kBlock + threadIdx.x;
-  const long long off = n * blockIdx.y;
-  if (i < n) {
-    const float fv = (float)r[off + i];
-    f32[off + i] = fv;
-    u[off + i] = wdinv[(unsigned)i / 3] * fv;  // r is zero at fixed DOFs
-  }
-}
-
 // Coarse right-hand side f_c = M_c P^T r (see restrict_node); with wdc set,
 // also the coarse level's first Jacobi sweep from zero, tc = wdc * f_c.
 // (bx, rhs): the workgroup's place in a launch of (ceil(C.nn / kBlock), nrhs).
@@ -421,7 +409,7 @@ __global__ void k_reduce_final(const double* __restrict__ partials, double* __re
   if (threadIdx.x == 0) out[(long long)stride * blockIdx.x] = s;
 }
 
-// block r: out[r] = sum of parts[r][0 .. n) in a fixed order (the partials of
+// block r: out[r * stride] = sum of parts[r][0 .. n) in a fixed order (the partials of
 // a streaming-kernel launch with more workgroups than a vector kernel's block
 // should sum on its own); skipped for an inactive right-hand side.  One block
 // of 1024 threads with eight independent chains each keeps enough loads in
@@ -439,7 +427,8 @@ __device__ inline long long vec_chunk(long long n) {
   return ((m + ranges - 1) / ranges + kBlock - 1) / kBlock * kBlock;
 }
 __global__ __launch_bounds__(kSumThreads) void k_sum_parts(const double* __restrict__ parts, int n,
-                                                           double* __restrict__ out, const int* __restrict__ act) {
+                                                           double* __restrict__ out, int stride,
+                                                           const int* __restrict__ act) {
   if (act && !act[blockIdx.x]) return;
   parts += (long long)n * blockIdx.x;
   double a[8];
@@ -459,28 +448,42 @@ __global__ __launch_bounds__(kSumThreads) void k_sum_parts(const double* __restr
     double t = 0.0;
 #pragma unroll
     for (int w = 0; w < kSumThreads / 64; ++w) t += part[w];
-    out[blockIdx.x] = t;
+    out[(long long)stride * blockIdx.x] = t;
   }
 }
 
-// grid (kReduceBlocks, nrhs): r = M f (fixed DOFs zeroed), x = 0 and the
-// partials of ||r||^2 (the summation order of k_dot_partial)
-__global__ void k_pcg_start(Level L, const double* __restrict__ f, double* __restrict__ r, double* __restrict__ x,
-                            double* __restrict__ partials) {
+// grid (kReduceBlocks, nrhs): r = M f (fixed DOFs zeroed), the partials of
+// ||r||^2 (the summation order of k_dot_partial), and what the first preconditioner
+// reads of r: its binary32 copy f32 (mixed precision) and the first sweep from
+// zero t (either may be null).  x is not touched: the first update writes it
+// (x_zero: it is cleared here instead, for the form whose residual replacement reads it).
+template <typename TW>
+__global__ void k_pcg_start(Level L, const double* __restrict__ f, double* __restrict__ r, double* __restrict__ x_zero,
+                            double* __restrict__ partials, const TW* __restrict__ wdinv, float* __restrict__ f32,
+                            TW* __restrict__ t) {
   const long long n = 3ll * L.nn;
   const long long off = n * blockIdx.y;
   f += off;
   r += off;
-  x += off;
+  if (x_zero) x_zero += off;
+  if (f32) f32 += off;
+  if (t) t += off;
   partials += (long long)kReduceBlocks * blockIdx.y;
   double acc = 0.0;
 #pragma unroll 4
   for (long long i = (long long)blockIdx.x * kBlock + threadIdx.x; i < n; i += (long long)gridDim.x * kBlock) {
-    const int node = (int)(i / 3), c = (int)(i % 3);
+    const int node = (int)((unsigned)i / 3), c = (int)((unsigned)i % 3);
     const double ri = ((L.mask[node] >> c) & 1) ? 0.0 : f[i];
     r[i] = ri;
-    x[i] = 0.0;
+    if (x_zero) x_zero[i] = 0.0;
     acc += ri * ri;
+    if constexpr (sizeof(TW) == 4) {
+      const float fv = (float)ri;
+      f32[i] = fv;
+      if (t) t[i] = wdinv[node] * fv;
+    } else {
+      if (t) t[i] = wdinv[node] * ri;
+    }
   }
   acc = block_sum(acc);
   if (threadIdx.x == 0) partials[blockIdx.x] = acc;
@@ -541,6 +544,32 @@ __global__ void k_pcg_final_sums(const double* __restrict__ pa, const double* __
   const double* p = (blockIdx.y ? pb : pa) + (long long)kReduceBlocks * blockIdx.x;
   const double v = sum_partials(p);
   if (threadIdx.x == 0) sc[kScalars * blockIdx.x + (blockIdx.y ? kTmp2 : kTmp)] = v;
+}
+// the same from the n pairs (a, b) per right-hand side of a kFinal launch
+__global__ __launch_bounds__(kSumThreads) void k_pcg_final_pairs(const double2* __restrict__ parts, int n,
+                                                                 double* __restrict__ sc) {
+  parts += (long long)n * blockIdx.x;
+  double a = 0.0, b = 0.0;
+#pragma unroll 8
+  for (int i = threadIdx.x; i < n; i += kSumThreads) {
+    const double2 v = parts[i];
+    a += v.x;
+    b += v.y;
+  }
+  __shared__ double part[kSumThreads / 64][2];
+  a = wave_sum(a);
+  b = wave_sum(b);
+  if ((threadIdx.x & 63) == 0) {
+    part[threadIdx.x >> 6][0] = a;
+    part[threadIdx.x >> 6][1] = b;
+  }
+  __syncthreads();
+  if (threadIdx.x < 2) {
+    double t = 0.0;
+#pragma unroll
+    for (int w = 0; w < kSumThreads / 64; ++w) t += part[w][threadIdx.x];
+    sc[kScalars * blockIdx.x + (threadIdx.x ? kTmp2 : kTmp)] = t;
+  }
 }
 
 // grid (kReduceBlocks, nrhs).  alpha = rz / pq with pq the sum of npq partials
@@ -711,12 +740,13 @@ __device__ __forceinline__ void update_px_block(long long n, const double* __res
     p32b += off;
     if (parity) {
       const double a_odd = s[kAlphaP], a_even = s[kAlphaP + 1];
+      const bool fresh = s[kIts] == 2.0;  // x has not been written yet
       for (long long b0 = bx * chunk; b0 < n; b0 += gx * chunk) {
         const long long e = min(b0 + chunk, n);
 #pragma unroll 4
         for (long long i = b0 + threadIdx.x; i < e; i += kBlock) {
           const double po = (double)p32[i], pe = (double)p32b[i];
-          double xi = x[i];
+          double xi = fresh ? 0.0 : x[i];
           xi += a_odd * po;
           xi += a_even * pe;
           x[i] = xi;
@@ -734,6 +764,7 @@ __device__ __forceinline__ void update_px_block(long long n, const double* __res
     return;
   }
   p += off;
+  const bool fresh = !p32 && s[kIts] == 1.0;  // x has not been written yet
   for (long long b0 = bx * chunk; b0 < n; b0 += gx * chunk) {
     const long long e = min(b0 + chunk, n);
     if (p32) {
@@ -749,7 +780,7 @@ __device__ __forceinline__ void update_px_block(long long n, const double* __res
 #pragma unroll 4
       for (long long i = b0 + threadIdx.x; i < e; i += kBlock) {
         const double pi = p[i];
-        x[i] += alpha * pi;
+        x[i] = (fresh ? 0.0 : x[i]) + alpha * pi;
         p[i] = (double)z[i] + beta * pi;
       }
     }
@@ -836,53 +867,48 @@ __global__ void k_pcg_restart(double* __restrict__ sc, int* __restrict__ active,
 }
 
 // grid (kReduceBlocks, nrhs): the x += alpha p still due when the solve stops
-// (act, may be null: only the right-hand sides whose flag is set)
-template <typename TP>
-__global__ void k_flush_x(long long n, const double* __restrict__ sc, const TP* __restrict__ p,
-                          double* __restrict__ x, const int* __restrict__ act) {
+// (act, may be null: only the right-hand sides whose flag is set).  fresh_its: x
+// has not been written before iteration fresh_its + 1's update, so up to it the
+// result is written from zero (also with nothing due); -1: x was cleared.
+__global__ void k_flush_x(long long n, const double* __restrict__ sc, const double* __restrict__ p,
+                          double* __restrict__ x, const int* __restrict__ act, double fresh_its) {
   const int rhs = blockIdx.y;
   const double* s = sc + kScalars * rhs;
-  if (s[kXPend] == 0.0 || (act && !act[rhs])) return;
-  const double alpha = s[kAlpha];
+  const bool fresh = s[kIts] <= fresh_its;
+  const double alpha = s[kXPend] != 0.0 ? s[kAlpha] : 0.0;
+  if ((s[kXPend] == 0.0 && !fresh) || (act && !act[rhs])) return;
+  const bool zero = s[kXPend] == 0.0;
   const long long off = n * rhs;
   p += off;
   x += off;
 #pragma unroll 4
   for (long long i = (long long)blockIdx.x * kBlock + threadIdx.x; i < n; i += (long long)gridDim.x * kBlock)
-    x[i] += alpha * (double)p[i];
+    x[i] = zero ? 0.0 : (fresh ? 0.0 : x[i]) + alpha * p[i];
 }
 // The same for the binary32 directions of the mixed form (launch_update_px):
 // after the last iteration k, p_k (p32 for odd k) is pending, and for even k
-// p_(k-1) (p32) before it; a breakdown left its alpha 0.
+// p_(k-1) (p32) before it; a breakdown left its alpha 0.  x is first written
+// after iteration 2 (when the solve goes on), so up to k = 2 the result starts from zero.
 __global__ void k_flush_x_pair(long long n, const double* __restrict__ sc, const float* __restrict__ p32,
                                const float* __restrict__ p32b, double* __restrict__ x, const int* __restrict__ act) {
   const int rhs = blockIdx.y;
   const double* s = sc + kScalars * rhs;
   const long long k = (long long)s[kIts];
-  if (k == 0 || (act && !act[rhs])) return;
-  const bool even = (k & 1) == 0;
-  const double a_odd = s[kAlphaP], a_even = s[kAlphaP + 1];
+  if (act && !act[rhs]) return;
+  const bool fresh = k <= 2, even = (k & 1) == 0;
+  const double a_odd = k > 0 ? s[kAlphaP] : 0.0, a_even = k > 0 && even ? s[kAlphaP + 1] : 0.0;
+  const bool odd_due = a_odd != 0.0, even_due = a_even != 0.0;
+  if (!odd_due && !even_due && !fresh) return;
   const long long off = n * rhs;
   p32 += off;
   p32b += off;
   x += off;
-  if (even && a_even == 0.0) {  // breakdown in the last iteration: only p_(k-1) is due
-    if (a_odd == 0.0) return;
 #pragma unroll 4
-    for (long long i = (long long)blockIdx.x * kBlock + threadIdx.x; i < n; i += (long long)gridDim.x * kBlock)
-      x[i] += a_odd * (double)p32[i];
-  } else if (even) {
-#pragma unroll 4
-    for (long long i = (long long)blockIdx.x * kBlock + threadIdx.x; i < n; i += (long long)gridDim.x * kBlock) {
-      double xi = x[i];
-      xi += a_odd * (double)p32[i];
-      xi += a_even * (double)p32b[i];
-      x[i] = xi;
-    }
-  } else if (a_odd != 0.0) {
-#pragma unroll 4
-    for (long long i = (long long)blockIdx.x * kBlock + threadIdx.x; i < n; i += (long long)gridDim.x * kBlock)
-      x[i] += a_odd * (double)p32[i];
+  for (long long i = (long long)blockIdx.x * kBlock + threadIdx.x; i < n; i += (long long)gridDim.x * kBlock) {
+    double xi = fresh ? 0.0 : x[i];
+    if (odd_due) xi += a_odd * (double)p32[i];
+    if (even_due) xi += a_even * (double)p32b[i];
+    x[i] = xi;
   }
 }
 
@@ -968,11 +994,6 @@ template void launch_jacobi_first<double>(const Level&, const double*, const dou
                                           hipStream_t);
 template void launch_jacobi_first<float>(const Level&, const float*, const float*, float*, int, const int*,
                                          hipStream_t);
-void launch_jacobi_first_from64(long long n, const float* wdinv, const double* r, float* f32, float* u, int nrhs,
-                                const int* act, hipStream_t s) {
-  k_jacobi_first_from64<<<dim3(blocks_for(n), nrhs), kBlock, 0, s>>>(n, wdinv, r, f32, u, act);
-}
-
 template <typename T>
 void launch_restrict(const Level& F, const Level& C, const T* r, T* fc, int nrhs, const int* act, hipStream_t s,
                      const T* wdc, T* tc) {
@@ -1043,16 +1064,21 @@ void launch_dot_partial(long long n, const double* x, const double* y, double* p
                         hipStream_t s) {
   k_dot_partial<<<dim3(kReduceBlocks, nrhs), kBlock, 0, s>>>(n, x, y, partials, act);
 }
-void launch_sum_parts(const double* parts, int n, double* out, int nrhs, const int* act, hipStream_t s) {
-  k_sum_parts<<<nrhs, kSumThreads, 0, s>>>(parts, n, out, act);
+void launch_sum_parts(const double* parts, int n, double* out, int nrhs, const int* act, hipStream_t s, int stride) {
+  k_sum_parts<<<nrhs, kSumThreads, 0, s>>>(parts, n, out, stride, act);
 }
 void launch_reduce_final(const double* partials, double* out, int stride, int nrhs, hipStream_t s) {
   k_reduce_final<<<nrhs, kBlock, 0, s>>>(partials, out, stride);
 }
-void launch_pcg_start(const Level& L, const double* f, double* r, double* x, double* partials, int nrhs,
-                      hipStream_t s) {
-  k_pcg_start<<<dim3(kReduceBlocks, nrhs), kBlock, 0, s>>>(L, f, r, x, partials);
+template <typename TW>
+void launch_pcg_start(const Level& L, const double* f, double* r, double* x_zero, double* partials, const TW* wdinv,
+                      float* f32, TW* t, int nrhs, hipStream_t s) {
+  k_pcg_start<TW><<<dim3(kReduceBlocks, nrhs), kBlock, 0, s>>>(L, f, r, x_zero, partials, wdinv, f32, t);
 }
+template void launch_pcg_start<float>(const Level&, const double*, double*, double*, double*, const float*, float*,
+                                      float*, int, hipStream_t);
+template void launch_pcg_start<double>(const Level&, const double*, double*, double*, double*, const double*, float*,
+                                       double*, int, hipStream_t);
 void launch_pcg_init(double rtol2, const double* ff_partials, double* sc, int* active, int nrhs, hipStream_t s) {
   k_pcg_init<<<nrhs, kBlock, 0, s>>>(rtol2, ff_partials, sc, active);
 }
@@ -1060,6 +1086,9 @@ void launch_pcg_final(const Level& L, const double* f, const double* q, const do
                       double* sc, int nrhs, hipStream_t s) {
   k_pcg_final_dots<<<dim3(kReduceBlocks, nrhs), kBlock, 0, s>>>(L, f, q, x, pa, pb);
   k_pcg_final_sums<<<dim3(nrhs, 2), kBlock, 0, s>>>(pa, pb, sc);
+}
+void launch_pcg_final_pairs(const double* parts, int n, double* sc, int nrhs, hipStream_t s) {
+  k_pcg_final_pairs<<<nrhs, kSumThreads, 0, s>>>(reinterpret_cast<const double2*>(parts), n, sc);
 }
 template <typename TW, typename TQ>
 void launch_update_r_first(long long n, const double* pq_partials, int npq, double* sc, const int* active,
@@ -1104,13 +1133,11 @@ template void launch_update_px<double>(long long, const double*, int, double*, c
 template void launch_update_px<float>(long long, const double*, int, double*, const int*, const float*, double*,
                                       double*, int, int, hipStream_t, float*, float*);
 void launch_flush_x(long long n, const double* sc, const double* p, double* x, int nrhs, hipStream_t s,
-                    const int* act, const float* p32, const float* p32b) {
+                    const int* act, const float* p32, const float* p32b, bool cleared) {
   if (p)
-    k_flush_x<double><<<dim3(kReduceBlocks, nrhs), kBlock, 0, s>>>(n, sc, p, x, act);
-  else if (p32b)
-    k_flush_x_pair<<<dim3(kReduceBlocks, nrhs), kBlock, 0, s>>>(n, sc, p32, p32b, x, act);
+    k_flush_x<<<dim3(kReduceBlocks, nrhs), kBlock, 0, s>>>(n, sc, p, x, act, cleared ? -1.0 : 1.0);
   else
-    k_flush_x<float><<<dim3(kReduceBlocks, nrhs), kBlock, 0, s>>>(n, sc, p32, x, act);
+    k_flush_x_pair<<<dim3(kReduceBlocks, nrhs), kBlock, 0, s>>>(n, sc, p32, p32b, x, act);
 }
 void launch_dot_mixed(long long n, const float* u32, const double* r, double* partials, int nrhs, const int* act,
                       hipStream_t s) {

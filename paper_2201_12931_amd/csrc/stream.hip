@@ -207,7 +207,9 @@ __device__ inline double select_bit(int m, int c, double a, double b) { return (
 // PRE > 0: zchunk is PRE and all inputs of the workgroup are requested up front.
 // DOT (K u and the sweep, without MASKIN): also one partial per workgroup
 // into dotp, of u . (A u) for K u and of f . y (the right-hand side times the
-// new iterate) for the sweep.
+// new iterate) for the sweep.  kFinal (always DOT): nothing but a pair of partials, of ||M f -
+// A u||^2 and f . u, so that the true residual of a solve takes one pass over f and
+// u instead of writing A u and reading all three.
 // TU: the type u is stored in (T, or binary32 widened on load for the
 // binary64 product on a binary32 search direction).
 // One workgroup's tile: (bx, by, bz) is its place in the grid's launch of
@@ -226,7 +228,7 @@ __device__ __forceinline__ void stream_tile(const Level& L, const HaarCoef<T>& q
   {  // bz = z-chunk + nchunks * right-hand side; vectors are [nrhs][3 nn]
     const long long off = 3ll * L.nn * (bz / nchunks);
     ug += off;
-    yg += off;
+    if (MODE != kFinal) yg += off;
     if (MODE != kApply) fg += off;
   }
   const int lane = threadIdx.x & 63;
@@ -332,7 +334,7 @@ __device__ __forceinline__ void stream_tile(const Level& L, const HaarCoef<T>& q
     }
   }
   // With DOT: this thread's share of the dot product over its outputs.
-  double dot = 0.0;
+  double dot = 0.0, dot2 = 0.0;
 
   // Inputs of the epilogue of iteration kk (output plane kk-1): support bits,
   // f and omega/D.
@@ -365,7 +367,8 @@ __device__ __forceinline__ void stream_tile(const Level& L, const HaarCoef<T>& q
                   const T (&fo)[R][3], const T (&wo)[R], const T (&Fin)[R][4][3], T (&Fout)[R][4][3],
                   const T (&Tin)[R][4][3], T (&Tout)[R][4][3]) {
     const bool out_plane = kk - 1 >= kc0 && kk - 1 < kc1;
-    const Rsrc ry = plane_rsrc(yg + 3 * plane * (out_plane ? kk - 1 : 0), out_plane ? vbytes : 0);
+    const Rsrc ry = plane_rsrc(MODE == kFinal ? fg : yg + 3 * plane * (out_plane ? kk - 1 : 0),
+                               MODE != kFinal && out_plane ? vbytes : 0);
     // u of plane kk (fixed DOFs masked when the input may be non-zero there)
     // (a wave-uniform test skips the selects for rows without fixed DOFs)
     T ue[R + 1][3];
@@ -415,10 +418,17 @@ __device__ __forceinline__ void stream_tile(const Level& L, const HaarCoef<T>& q
           const T wr = MASKIN ? select_bit(mo[r], c, T(L.omega), wo[r]) : wo[r];
           v[c] = uo[r][c] + wr * (fo[r][c] - Au);
           if (DOT && out_plane && offo[r] != kOutside) dot += (double)fo[r][c] * (double)v[c];
+        } else if (MODE == kFinal) {
+          // outside the output window f, the support bits and u read as 0, A u does not
+          if (out_plane && offo[r] != kOutside) {
+            const double ri = (double)(((mo[r] >> c) & 1) ? T(0) : fo[r][c]) - (double)Au;
+            dot += ri * ri;
+            dot2 += (double)fo[r][c] * (double)uo[r][c];
+          }
         } else
           v[c] = fo[r][c] - Au;
       }
-      store3(ry, offo[r], v);
+      if (MODE != kFinal) store3(ry, offo[r], v);
     };
     T xa[2][3], xb[2][3];
     xedge(0, xa);
@@ -577,18 +587,33 @@ __device__ __forceinline__ void stream_tile(const Level& L, const HaarCoef<T>& q
     }
   }
   if (DOT) {  // one partial per workgroup, in a fixed order
-    __shared__ double wsum[W];
+    __shared__ double wsum[W][2];
 #pragma unroll
-    for (int off = 32; off > 0; off >>= 1) dot += __shfl_down(dot, off, 64);
-    if (lane == 0) wsum[w] = dot;
+    for (int off = 32; off > 0; off >>= 1) {
+      dot += __shfl_down(dot, off, 64);
+      if (MODE == kFinal) dot2 += __shfl_down(dot2, off, 64);
+    }
+    if (lane == 0) {
+      wsum[w][0] = dot;
+      if (MODE == kFinal) wsum[w][1] = dot2;
+    }
     __syncthreads();
     if (threadIdx.x == 0) {
-      double t = 0.0;
+      double t = 0.0, t2 = 0.0;
 #pragma unroll
-      for (int k = 0; k < W; ++k) t += wsum[k];
+      for (int k = 0; k < W; ++k) {
+        t += wsum[k][0];
+        if (MODE == kFinal) t2 += wsum[k][1];
+      }
       const int parts = gx * gy * nchunks;
       const int rhs = bz / nchunks;
-      dotp[(long long)parts * rhs + bx + gx * (by + gy * (bz % nchunks))] = t;
+      const long long at = (long long)parts * rhs + bx + gx * (by + gy * (bz % nchunks));
+      if (MODE == kFinal) {
+        dotp[2 * at] = t;
+        dotp[2 * at + 1] = t2;
+      } else {
+        dotp[at] = t;
+      }
     }
   }
 }
@@ -656,7 +681,11 @@ void launch_stream_mode(int mode, dim3 grid, dim3 block, const Level& L, const H
   else if (mode == kSmooth)
     launch_timed(k_stream<T, kSmooth, R, W, MINW, MASKIN, PRE, false>, grid, block, s, t, L, q, E, u, f, wd, y,
                  zchunk, nchunks, act, nullptr);
-  else
+  else if (mode == kFinal) {
+    if constexpr (sizeof(T) == 8 && !MASKIN)
+      launch_timed(k_stream<T, kFinal, R, W, MINW, false, PRE, true>, grid, block, s, t, L, q, E, u, f, wd, y, zchunk,
+                   nchunks, act, dotp);
+  } else
     launch_timed(k_stream<T, kResidual, R, W, MINW, MASKIN, PRE, false>, grid, block, s, t, L, q, E, u, f, wd, y,
                  zchunk, nchunks, act, nullptr);
 }
@@ -842,6 +871,11 @@ void launch_stream_batch_impl(int mode, bool pre, bool dot, const Batch<StreamTa
     else if (pre) k_stream_batch<T, kSmooth, R, W, MINW, 1, false><<<grid, block, 0, s>>>(b, q);
     else if (dot) k_stream_batch<T, kSmooth, R, W, MINW, 0, true><<<grid, block, 0, s>>>(b, q);
     else k_stream_batch<T, kSmooth, R, W, MINW, 0, false><<<grid, block, 0, s>>>(b, q);
+  } else if (mode == kFinal) {
+    if constexpr (sizeof(T) == 8) {
+      if (pre) k_stream_batch<T, kFinal, R, W, MINW, 1, true><<<grid, block, 0, s>>>(b, q);
+      else k_stream_batch<T, kFinal, R, W, MINW, 0, true><<<grid, block, 0, s>>>(b, q);
+    }
   } else {
     if (pre) k_stream_batch<T, kResidual, R, W, MINW, 1, false><<<grid, block, 0, s>>>(b, q);
     else k_stream_batch<T, kResidual, R, W, MINW, 0, false><<<grid, block, 0, s>>>(b, q);
