@@ -318,7 +318,10 @@ int hexmg_element_matrix(double nu, double *Ke_host);
  * made by timing the candidates (node-gather; every streaming shape with 1..128
  * planes per chunk -- a chunk of one plane requests all its inputs before any
  * arithmetic) with max_nrhs right-hand sides on the grid's stream during the first
- * successful hexmg_set_density, separately for K u, the sweep and the residual. */
+ * successful hexmg_set_density, separately for K u, the sweep and the residual.
+ * V-cycles with two sweeps and re-discretized operators run levels of up to 6000
+ * nodes (times max_nrhs) in fused steps of their own, a launch down and a launch up,
+ * unless hexmg_set_kernel_choice was called for the level; K u still takes the choice reported here. */
 int hexmg_kernel_choice(hexmg_grid_t grid, int level, int dtype, int mode, int *kernel, int *zchunk, int *shape);
 
 /* Overrides the element-product kernel of `level` for dtype (all three

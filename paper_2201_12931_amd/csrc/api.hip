@@ -192,7 +192,8 @@ inline unsigned long long batch_sig(int kind, int a = 0, int b = 0, int c = 0, i
          ((unsigned long long)(b & 0xff) << 16) | ((unsigned long long)(c & 0xff) << 24) |
          ((unsigned long long)(d & 0xff) << 32) | ((unsigned long long)(e & 0xff) << 40);
 }
-enum BatchKind { kBkStream, kBkRestrict, kBkProlong, kBkGemv, kBkUpdateR, kBkRrCheck, kBkUpdatePx, kBkStreamU32 };
+enum BatchKind { kBkStream, kBkRestrict, kBkProlong, kBkGemv, kBkUpdateR, kBkRrCheck, kBkUpdatePx, kBkStreamU32,
+                 kBkTileDown, kBkTileUp };
 
 // smooth1: the sweep on the first sweep from zero, formed on load (kSmoothFirst)
 const char* kFamilies[] = {"apply_f64", "apply_f32", "smooth_f64", "smooth_f32", "residual_f64",
@@ -758,15 +759,56 @@ void wait_coarse(hexmg_grid* g, hipStream_t s) {
   g->coarse_waited_valid = true;
 }
 
+// Whether level l takes the fused steps of the small levels (tile.hip): two
+// sweeps, re-discretized operators, a kernel choice left to the library, and up to
+// kTileNodes nodes (counted per right-hand side).  With the limit at 6000 a state
+// at 32x16x16 (binary64) takes 1140 us against 1253 step by step, one at 128x64x64
+// (mixed) 2189 against about 2300.  At 1e4 nodes the repeated work of the halos has caught
+// up with the launches: 1146 us at 32x16x16, and eight uneven grids solved together,
+// whose step launches are shared, 3798 against 3426 us.  Level 0 of the public V-cycle
+// (maskin), whose right-hand side may be non-zero at fixed DOFs, is launched step by step.
+constexpr long long kTileNodes = 6000;
+template <typename T>
+bool use_tiles(const hexmg_grid* g, int l, bool maskin = false) {
+  return g->tiles_ok && !g->galerkin && g->desc.kernel == HEXMG_KERNEL_AUTO && g->desc.smooth_sweeps == 2 &&
+         l < g->L - 1 && !(l == 0 && maskin) && !(sizeof(T) == 4 ? g->set32 : g->set64)[l] &&
+         (long long)g->lv[l].nn * g->desc.max_nrhs <= kTileNodes;
+}
+
 // Whether the level-0 pre-smoothing forms the first sweep from zero on load
 // (kSmoothFirst: the second sweep reads f and omega/D instead of the first's
 // output), so that the CG residual update writes no first sweep: two or more
 // sweeps, and a streaming sweep kernel with such a form.
 template <typename T>
 bool first_fused(const hexmg_grid* g) {
+  if (use_tiles<T>(g, 0)) return true;
   if (!g->desc.fuse_first || g->L < 2 || g->desc.smooth_sweeps < 2) return false;
   const hexmg_grid::Choice& ch = (sizeof(T) == 4 ? g->choice32 : g->choice64)[0][kSmooth];
   return ch.kernel == HEXMG_KERNEL_STREAM && first_shape_ok(sizeof(T) == 4, ch.shape);
+}
+
+template <typename T>
+void vcycle_level(hexmg_grid* g, VView<T>& v, int l, const T* f, T* out, int nrhs, const int* act, hipStream_t s,
+                  bool first_done = false, bool maskin = false, double* dotp = nullptr);
+
+// Whether the level below l reads its first sweep from v.t: not the coarsest one,
+// and not one whose fused steps form it from f (unless the cooperative launch starts there).
+template <typename T>
+bool next_reads_first(const hexmg_grid* g, int l) {
+  return l + 1 < g->L - 1 && ((sizeof(T) == 4 ? g->tail32 : g->tail64) == l + 1 || !use_tiles<T>(g, l + 1));
+}
+// The cycle below level l, from v.f[l + 1] to v.u[l + 1].
+template <typename T>
+void below(hexmg_grid* g, VView<T>& v, int l, int nrhs, const int* act, hipStream_t s) {
+  int& tail = sizeof(T) == 4 ? g->tail32 : g->tail64;
+  const int blocks = sizeof(T) == 4 ? g->tail_blocks32 : g->tail_blocks64;
+  if (l + 1 < g->L - 1 && tail == l + 1) {  // the rest of the cycle as one cooperative launch
+    wait_coarse(g, s);
+    if (launch_coarse_cycle<T>(make_cycle<T>(g), l + 1, nrhs, act, blocks, s) == hipSuccess) return;
+    (void)hipGetLastError();
+    tail = 0;  // not launchable here: back to one launch per step from now on
+  }
+  vcycle_level<T>(g, v, l + 1, v.f[l + 1], v.u[l + 1], nrhs, act, s, true);
 }
 
 // out = V_l(f) from a zero initial guess.  The first sweep writes the level's
@@ -778,7 +820,7 @@ bool first_fused(const hexmg_grid* g) {
 // (the deeper levels' right-hand sides come out of the masked restriction).
 template <typename T>
 void vcycle_level(hexmg_grid* g, VView<T>& v, int l, const T* f, T* out, int nrhs, const int* act, hipStream_t s,
-                  bool first_done = false, bool maskin = false, double* dotp = nullptr) {
+                  bool first_done, bool maskin, double* dotp) {
   const Level& L = g->lv[l];
   if (l == g->L - 1) {
     wait_coarse(g, s);
@@ -789,6 +831,47 @@ void vcycle_level(hexmg_grid* g, VView<T>& v, int l, const T* f, T* out, int nrh
         g, kStCoarse, s, batch_sig(kBkGemv, sizeof(T)), task, task.gx * nrhs,
         [=](hipStream_t st) { launch_coarse_gemv<T>(nc, Ainv, f, out, nrhs, act, st); },
         [](const Batch<GemvTask<T>>& b, const BatchParams&, hipStream_t st) { launch_coarse_gemv_batch<T>(b, st); });
+    return;
+  }
+  if (use_tiles<T>(g, l, maskin)) {
+    constexpr bool f32 = sizeof(T) == 4;
+    const T* E = f32 ? (const T*)g->E32[l] : (const T*)g->E64[l];
+    const void* kq = f32 ? (const void*)&g->k032 : (const void*)&g->k064;
+    const K0Coef<T> k0 = *static_cast<const K0Coef<T>*>(kq);
+    const unsigned long long cls = (unsigned long long)g->rec_class << 48;
+    const int blocks = tile_count(L) * nrhs;
+    const bool first = next_reads_first<T>(g, l);
+    TileDownTask<T> down{L, E, f, v.wd[l], v.t[l], g->lv[l + 1].mask, v.f[l + 1], first ? v.wd[l + 1] : nullptr,
+                         first ? v.t[l + 1] : nullptr, act};
+    emit_task<TileDownTask<T>>(
+        g, st_down(l, 1), s, batch_sig(kBkTileDown, sizeof(T)) | cls, down, blocks,
+        [=](hipStream_t st) {
+          Batch<TileDownTask<T>> b;
+          b.n = 1;
+          b.begin[1] = blocks;
+          b.a[0] = down;
+          launch_tile_down<T>(b, k0, st);
+        },
+        [](const Batch<TileDownTask<T>>& b, const BatchParams& p, hipStream_t st) {
+          launch_tile_down<T>(b, *static_cast<const K0Coef<T>*>(p.q), st);
+        },
+        BatchParams{0, 0, false, false, kq});
+    below<T>(g, v, l, nrhs, act, s);
+    TileUpTask<T> up{L, E, f, v.wd[l], v.t[l], v.u[l + 1], out, act, dotp};
+    const bool dot = dotp != nullptr;
+    emit_task<TileUpTask<T>>(
+        g, st_up(l, 1), s, batch_sig(kBkTileUp, sizeof(T), dot) | cls, up, blocks,
+        [=](hipStream_t st) {
+          Batch<TileUpTask<T>> b;
+          b.n = 1;
+          b.begin[1] = blocks;
+          b.a[0] = up;
+          launch_tile_up<T>(dot, b, k0, st);
+        },
+        [](const Batch<TileUpTask<T>>& b, const BatchParams& p, hipStream_t st) {
+          launch_tile_up<T>(p.dot, b, *static_cast<const K0Coef<T>*>(p.q), st);
+        },
+        BatchParams{0, 0, false, dot, kq});
     return;
   }
   const int nu = g->desc.smooth_sweeps;
@@ -811,8 +894,8 @@ void vcycle_level(hexmg_grid* g, VView<T>& v, int l, const T* f, T* out, int nrh
   }
   g->stage = st_down(l, 90);
   gather<T>(g, kResidual, l, buf[cur], f, v.wd[l], v.r[l], nrhs, s, maskin, act);
-  // the next level's first sweep is formed inside the restriction (not on the coarsest level)
-  const bool fuse = l + 1 < g->L - 1;
+  // the next level's first sweep is formed inside the restriction where that level reads it
+  const bool fuse = next_reads_first<T>(g, l);
   {
     const Level F = L, C = g->lv[l + 1];
     RestrictTask<T> task{F, C, v.r[l], v.f[l + 1], act, fuse ? v.wd[l + 1] : nullptr, fuse ? v.t[l + 1] : nullptr,
@@ -822,18 +905,7 @@ void vcycle_level(hexmg_grid* g, VView<T>& v, int l, const T* f, T* out, int nrh
         [=](hipStream_t st) { launch_restrict<T>(F, C, task.r, task.fc, nrhs, act, st, task.wdc, task.tc); },
         [](const Batch<RestrictTask<T>>& b, const BatchParams&, hipStream_t st) { launch_restrict_batch<T>(b, st); });
   }
-  int& tail = sizeof(T) == 4 ? g->tail32 : g->tail64;
-  const int blocks = sizeof(T) == 4 ? g->tail_blocks32 : g->tail_blocks64;
-  bool done = false;
-  if (fuse && tail == l + 1) {  // the rest of the cycle as one cooperative launch
-    wait_coarse(g, s);
-    done = launch_coarse_cycle<T>(make_cycle<T>(g), l + 1, nrhs, act, blocks, s) == hipSuccess;
-    if (!done) {
-      (void)hipGetLastError();
-      tail = 0;  // not launchable here: back to one launch per step from now on
-    }
-  }
-  if (!done) vcycle_level<T>(g, v, l + 1, v.f[l + 1], v.u[l + 1], nrhs, act, s, fuse);
+  below<T>(g, v, l, nrhs, act, s);
   {
     const Level F = L, C = g->lv[l + 1];
     ProlongTask<T> task{F, C, v.u[l + 1], buf[cur], act, prolong_blocks(F), prolong_slab(F)};
@@ -855,6 +927,7 @@ void vcycle_level(hexmg_grid* g, VView<T>& v, int l, const T* f, T* out, int nrh
 template <typename T>
 int sweep_dot_parts(const hexmg_grid* g) {
   if (g->L < 2) return 0;
+  if (use_tiles<T>(g, 0)) return tile_count(g->lv[0]) <= kMaxDotParts ? tile_count(g->lv[0]) : 0;
   const hexmg_grid::Choice& ch = (sizeof(T) == 4 ? g->choice32 : g->choice64)[0][kSmooth];
   if (ch.kernel != HEXMG_KERNEL_STREAM) return 0;
   const int nb = stream_blocks(g->lv[0], sizeof(T) == 4, ch.shape, ch.zchunk);
@@ -1094,6 +1167,14 @@ int hexmg_grid_create(const hexmg_grid_desc* d, void* workspace, size_t bytes, v
   float Kf[576];
   element_matrix(d->nu, Ke);
   for (int i = 0; i < 576; ++i) Kf[i] = (float)Ke[i];
+  g->tiles_ok = k0_coefficients(Ke, &g->k064);
+  for (int i = 0; i < 2; ++i) {
+    for (int j = 0; j < 3; ++j) g->k032.d[i][j] = (float)g->k064.d[i][j];
+    g->k032.p[i] = (float)g->k064.p[i];
+    g->k032.m[i] = (float)g->k064.m[i];
+  }
+  g->set64.assign(g->L, 0);
+  g->set32.assign(g->L, 0);
   if (hipMemcpyAsync(g->Ke64, Ke, sizeof(Ke), hipMemcpyHostToDevice, s) != hipSuccess ||
       hipMemcpyAsync(g->Ke32, Kf, sizeof(Kf), hipMemcpyHostToDevice, s) != hipSuccess)
     return cleanup(fail(HEXMG_ERR_DEVICE, "copy of the element matrix failed"));
@@ -2029,6 +2110,7 @@ int hexmg_set_kernel_choice(hexmg_grid_t g, int level, int dtype, int kernel, in
     return fail(HEXMG_ERR_INVALID, "bad kernel");
   }
   (dtype == HEXMG_F64 ? g->choice64 : g->choice32)[level].fill(c);
+  (dtype == HEXMG_F64 ? g->set64 : g->set32)[level] = 1;
   g->tuned = true;
   return 0;
 }

@@ -230,6 +230,49 @@ struct UpdatePxTask {
   float* p32;
   float* p32b;
 };
+// The fused steps of a small level (tile.hip): the way down (a sweep on the
+// first sweep from zero, the residual, its restriction) and the way up (the
+// prolongation and two sweeps) as one launch each.  The coarse level is the
+// fine one with half the elements per axis; cmask: its support bits.  u and out
+// are distinct vectors.
+template <typename T>
+struct TileDownTask {
+  Level F;
+  const T* E;
+  const T* f;
+  const T* wd;
+  T* u;
+  const uint8_t* cmask;
+  T* fc;
+  const T* wdc;
+  T* tc;
+  const int* act;
+};
+template <typename T>
+struct TileUpTask {
+  Level F;
+  const T* E;
+  const T* f;
+  const T* wd;
+  const T* u;
+  const T* ec;
+  T* out;
+  const int* act;
+  double* dotp;
+};
+// The ten distinct values of K0: d[axis c differs][other axes that differ] of equal
+// components, and of different ones p (the derivatives' signs agree both ways) or m,
+// by whether the third axis differs.
+template <typename T>
+struct K0Coef {
+  T d[2][3], p[2], m[2];
+};
+bool k0_coefficients(const double* Ke, K0Coef<double>* k);  // false if Ke has another form
+int tile_count(const Level& F);                             // workgroups per right-hand side
+template <typename T>
+void launch_tile_down(const Batch<TileDownTask<T>>& b, const K0Coef<T>& k, hipStream_t s);
+template <typename T>
+void launch_tile_up(bool dot, const Batch<TileUpTask<T>>& b, const K0Coef<T>& k, hipStream_t s);
 template <typename T>
 void launch_restrict_batch(const Batch<RestrictTask<T>>& b, hipStream_t s);
 template <typename T>
@@ -244,6 +287,8 @@ void launch_update_px_batch(const Batch<UpdatePxTask<TZ>>& b, hipStream_t s);
 // the task tables travel in the kernel arguments
 static_assert(sizeof(Batch<StreamTask<double>>) <= 4096, "stream task table too large for kernel arguments");
 static_assert(sizeof(Batch<RestrictTask<double>>) <= 4096, "restriction task table too large for kernel arguments");
+static_assert(sizeof(Batch<TileDownTask<double>>) + sizeof(K0Coef<double>) <= 4096, "tile task table too large");
+static_assert(sizeof(Batch<TileUpTask<double>>) + sizeof(K0Coef<double>) <= 4096, "tile task table too large");
 static_assert(sizeof(Batch<UpdateRTask<double, double>>) <= 4096, "update task table too large for kernel arguments");
 // workgroups per right-hand side of the single launches
 // and (transfers) the slabs of their banded order
@@ -536,6 +581,10 @@ struct hexmg_grid {
   std::vector<double> Gc_host;
   hexmg::HaarCoef<double> hq64;
   hexmg::HaarCoef<float> hq32;
+  bool tiles_ok = false;  // K0 has the ten-value form of the fused small-level steps
+  hexmg::K0Coef<double> k064;
+  hexmg::K0Coef<float> k032;
+  std::vector<char> set64, set32;  // levels whose kernel the caller set (they take no fused steps)
   // element-product kernel per level and precision ([level][0] binary64, [1] binary32)
   struct Choice { int kernel; int zchunk; int shape; };
   // [level][mode]: the element-product kernel per mode (K u, sweep, residual)
