@@ -1538,7 +1538,7 @@ struct PcgRun {
                              repl};
     const int b = nb;
     emit_task<UpdateRTask<TW, TQ>>(
-        g, kStEnd + 300, s, batch_sig(kBkUpdateR, sizeof(TW), sizeof(TQ)), task, kReduceBlocks * nb,
+        g, kStEnd + 300, s, batch_sig(kBkUpdateR, sizeof(TW), sizeof(TQ), vec_once(N())), task, kReduceBlocks * nb,
         [=](hipStream_t st) {
           launch_update_r_first<TW, TQ>(task.n, task.pq_partials, task.npq, task.sc, task.active, task.q, task.r,
                                         task.rr_partials, task.parity, task.wdinv, task.f32, task.t, b, st,
@@ -1547,14 +1547,15 @@ struct PcgRun {
         [](const Batch<UpdateRTask<TW, TQ>>& bt, const BatchParams&, hipStream_t st) { launch_update_r_first_batch<TW, TQ>(bt, st); });
   }
   template <typename TZ>
-  void emit_update_px(int nrz, int parity, const TZ* z, float* p32) {
-    UpdatePxTask<TZ> task{N(), g->partials, nrz, parity, g->scalars, g->active, z, g->p, u, p32, g->p32b};
+  void emit_update_px(int nrz, int k, const TZ* z, float* p32) {
+    const int fresh = g->p ? !p32 && k == 1 : k == 2;
+    UpdatePxTask<TZ> task{N(), g->partials, nrz, (k - 1) & 1, fresh, g->scalars, g->active, z, g->p, u, p32, g->p32b};
     const int b = nb;
     emit_task<UpdatePxTask<TZ>>(
-        g, kStEnd + 100, s, batch_sig(kBkUpdatePx, sizeof(TZ)), task, kReduceBlocks * nb,
+        g, kStEnd + 100, s, batch_sig(kBkUpdatePx, sizeof(TZ), vec_once(N())), task, kReduceBlocks * nb,
         [=](hipStream_t st) {
           launch_update_px<TZ>(task.n, task.rz_partials, task.nrz, task.sc, task.active, task.z, task.p, task.x,
-                               task.parity, b, st, task.p32, task.p32b);
+                               task.parity, task.fresh, b, st, task.p32, task.p32b);
         },
         [](const Batch<UpdatePxTask<TZ>>& bt, const BatchParams&, hipStream_t st) { launch_update_px_batch<TZ>(bt, st); });
   }
@@ -1565,10 +1566,10 @@ struct PcgRun {
     g->prof_tag = k + 1 - tag_off;
     if (g->desc.precision == HEXMG_FP64) {
       const int nrz = precondition(g, g->r, g->z, nullptr, g->partials, nb, g->active, s, true);
-      emit_update_px<double>(nrz, (k - 1) & 1, g->z, nullptr);
+      emit_update_px<double>(nrz, k, g->z, nullptr);
     } else {
       const int nrz = precondition(g, g->r, nullptr, g->vu32[0], g->partials, nb, g->active, s, true);
-      emit_update_px<float>(nrz, (k - 1) & 1, g->vu32[0], g->p32);  // mixed: the direction itself
+      emit_update_px<float>(nrz, k, g->vu32[0], g->p32);  // mixed: the direction itself
     }
     return issue_iteration(k + 1);
   }

@@ -221,7 +221,7 @@ template <typename TZ>
 struct UpdatePxTask {
   long long n;
   const double* rz_partials;
-  int nrz, parity;
+  int nrz, parity, fresh;
   double* sc;
   const int* active;
   const TZ* z;
@@ -306,6 +306,14 @@ void launch_sum_parts(const double* parts, int n, double* out, int nrhs, const i
 constexpr int kReduceBlocks = 1024;  // partial sums per reduction (fixed: deterministic)
 constexpr int kOcProbes = 32;       // Lagrange multipliers evaluated per OC pass
 constexpr int kBlock = 256;
+// CG's vector passes.  Up to vec_once unknowns a thread has at most kVecAhead
+// elements, in one range: the pass then requests them before it sums the partials
+// that its factor comes from, as each of the two waits is a good part of such a
+// pass (eight grids of 2.2 M unknowns together: r in 17 us, x and p in 16; 22 and 20 one
+// after the other).  Above, bandwidth bounds it, and a plain loop over the ranges is
+// faster (x and p at 768x384x384: 1.34 ms, 1.43 with the loads grouped ahead).
+constexpr int kVecAhead = 4;
+inline bool vec_once(long long n) { return n <= (long long)kReduceBlocks * kBlock * kVecAhead; }
 constexpr int kGJBlock = 64;  // pivot block of the coarsest inverse
 
 // ---- kernel launchers (kernels.hip) --------------------------------------
@@ -409,11 +417,12 @@ void launch_rr_check(const double* rr_partials, double* sc, int* active, double*
 // and in p32b when k is even, and x is brought up to date only after the even
 // iterations, by the two directions then pending (x += alpha_(k-1) p_(k-1),
 // then x += alpha_k p_k, the order and rounding of one update per iteration).
-// The first update of x (after iteration 1, with p null 2; s[kIts]) writes it from
-// zero without reading it, except with p and p32 both given (x cleared at the start).
+// fresh: this is the first update of x (after iteration 1, with p null 2), which
+// is then written from zero without reading it (not with p and p32 both
+// given: x is cleared at the start there).
 template <typename TZ>
 void launch_update_px(long long n, const double* rz_partials, int nrz, double* sc, const int* active, const TZ* z,
-                      double* p, double* x, int parity, int nrhs, hipStream_t s, float* p32 = nullptr,
+                      double* p, double* x, int parity, int fresh, int nrhs, hipStream_t s, float* p32 = nullptr,
                       float* p32b = nullptr);
 // x += alpha p for the right-hand sides where it is still due (s[kXPend]);
 // with p null, the binary32 directions still pending after the right-hand

@@ -35,21 +35,17 @@ __device__ inline double block_sum(double v) {
 }
 
 // Sum over a block of kBlock threads, returned to every thread (fixed order).
+// Once per kernel: the next call's writes do not wait for this one's reads.
 __device__ inline double block_sum_all(double v) {
   __shared__ double part[kBlock / 64];
-  __shared__ double total;
   v = wave_sum(v);
   const int w = threadIdx.x >> 6, lane = threadIdx.x & 63;
   if (lane == 0) part[w] = v;
   __syncthreads();
-  if (threadIdx.x == 0) {
-    double s = 0.0;
+  double s = 0.0;
 #pragma unroll
-    for (int i = 0; i < kBlock / 64; ++i) s += part[i];
-    total = s;
-  }
-  __syncthreads();
-  return total;
+  for (int i = 0; i < kBlock / 64; ++i) s += part[i];
+  return s;
 }
 
 // sum of the kReduceBlocks partials of one right-hand side, in every thread
@@ -426,6 +422,25 @@ __device__ inline long long vec_chunk(long long n) {
   const unsigned ranges = kReduceBlocks * rounds;
   return ((m + ranges - 1) / ranges + kBlock - 1) / kBlock * kBlock;
 }
+// One thread's part of the sum of v[0 .. n) over a block, in a fixed order with
+// eight loads in flight.
+__device__ inline double strided_sum(const double* __restrict__ v, int n) {
+  double s = 0.0;
+  int i = threadIdx.x;
+  for (; i + 7 * kBlock < n; i += 8 * kBlock) {
+    double a[8];
+#pragma unroll
+    for (int u = 0; u < 8; ++u) a[u] = v[i + u * kBlock];
+#pragma unroll
+    for (int u = 0; u < 8; ++u) s += a[u];
+  }
+  double a[8];
+#pragma unroll
+  for (int u = 0; u < 8; ++u) a[u] = i + u * kBlock < n ? v[i + u * kBlock] : 0.0;
+#pragma unroll
+  for (int u = 0; u < 8; ++u) s += a[u];
+  return s;
+}
 __global__ __launch_bounds__(kSumThreads) void k_sum_parts(const double* __restrict__ parts, int n,
                                                            double* __restrict__ out, int stride,
                                                            const int* __restrict__ act) {
@@ -583,8 +598,8 @@ __global__ __launch_bounds__(kSumThreads) void k_pcg_final_pairs(const double2* 
 // TQ: q in binary64, or the binary32 A p of the binary32 outer product
 // (widened on the fly).  repl (may be null): right-hand sides whose flag is
 // set get only alpha and the pending flag (their residual is replaced right
-// after, see k_replace_r).
-template <typename TW, typename TQ>
+// after, see k_replace_r).  ONCE: vec_once(n).
+template <typename TW, typename TQ, bool ONCE>
 __device__ __forceinline__ void update_r_first_block(long long n, const double* __restrict__ pq_partials, int npq,
                                                      double* __restrict__ sc, const int* __restrict__ active,
                                                      const TQ* __restrict__ q, double* __restrict__ r,
@@ -594,23 +609,8 @@ __device__ __forceinline__ void update_r_first_block(long long n, const double* 
                                                      int rhs) {
   constexpr int gx = kReduceBlocks;
   rr_partials += (long long)kReduceBlocks * rhs;
-  if (!active[rhs]) {
-    if (threadIdx.x == 0) rr_partials[bx] = 0.0;
-    return;
-  }
-  double pqs = 0.0;
-  for (int i = threadIdx.x; i < npq; i += kBlock) pqs += pq_partials[(long long)npq * rhs + i];
-  const double pq = block_sum_all(pqs);
-  double* s = sc + kScalars * rhs;
-  const double alpha = s[kRz0 + parity] / pq;
-  const bool ok = pq > 0.0 && pq < 1e308;
-  if (bx == 0 && threadIdx.x == 0) {
-    s[kPq] = pq;
-    s[kAlpha] = alpha;
-    s[kXPend] = ok ? 1.0 : 0.0;
-    s[kAlphaP + parity] = ok ? alpha : 0.0;
-  }
-  if (!ok || (repl && repl[rhs])) {  // breakdown: keep the previous iterate; the check flags it
+  const long long chunk = vec_chunk(n), first = bx * chunk, end = min(first + chunk, n);
+  if (first >= n || (!ONCE && !active[rhs])) {  // no elements for this block, or a right-hand side that has stopped
     if (threadIdx.x == 0) rr_partials[bx] = 0.0;
     return;
   }
@@ -619,42 +619,80 @@ __device__ __forceinline__ void update_r_first_block(long long n, const double* 
   r += off;
   if (f32) f32 += off;
   if (t) t += off;
-  double acc = 0.0;
-  const long long chunk = vec_chunk(n);
-  for (long long b0 = bx * chunk; b0 < n; b0 += gx * chunk) {
-    const long long e = min(b0 + chunk, n);
-#pragma unroll 4
-    for (long long i = b0 + threadIdx.x; i < e; i += kBlock) {
-      const double ri = r[i] - alpha * (double)q[i];
-      r[i] = ri;
-      acc += ri * ri;
-      if constexpr (sizeof(TW) == 4) {
-        const float fv = (float)ri;
-        f32[i] = fv;
-        if (t) t[i] = wdinv[(unsigned)i / 3] * fv;  // r is zero at fixed DOFs
-      } else {
-        if (t) t[i] = wdinv[(unsigned)i / 3] * ri;
+  double rv[kVecAhead], qv[kVecAhead];
+  TW wv[kVecAhead];
+  if constexpr (ONCE) {
+#pragma unroll
+    for (int u = 0; u < kVecAhead; ++u) {
+      const long long i = first + threadIdx.x + u * kBlock;
+      if (i < end) {
+        rv[u] = r[i];
+        qv[u] = (double)q[i];
+        if (t) wv[u] = wdinv[(unsigned)i / 3];
       }
+    }
+  }
+  double* s = sc + kScalars * rhs;
+  const int act = active[rhs], skip = repl ? repl[rhs] : 0;
+  const double rz0 = s[kRz0 + parity];
+  const double pq = block_sum_all(strided_sum(pq_partials + (long long)npq * rhs, npq));
+  const double alpha = rz0 / pq;
+  const bool ok = pq > 0.0 && pq < 1e308;
+  if (act && bx == 0 && threadIdx.x == 0) {
+    s[kPq] = pq;
+    s[kAlpha] = alpha;
+    s[kXPend] = ok ? 1.0 : 0.0;
+    s[kAlphaP + parity] = ok ? alpha : 0.0;
+  }
+  if (!act || !ok || skip) {  // breakdown: keep the previous iterate; the check flags it
+    if (threadIdx.x == 0) rr_partials[bx] = 0.0;
+    return;
+  }
+  double acc = 0.0;
+  auto element = [&](long long i, double r0, double q0, auto wd) {
+    const double ri = r0 - alpha * q0;
+    r[i] = ri;
+    acc += ri * ri;
+    if constexpr (sizeof(TW) == 4) {
+      const float fv = (float)ri;
+      f32[i] = fv;
+      if (t) t[i] = wd() * fv;  // r is zero at fixed DOFs
+    } else {
+      if (t) t[i] = wd() * ri;
+    }
+  };
+  if constexpr (ONCE) {
+#pragma unroll
+    for (int u = 0; u < kVecAhead; ++u) {
+      const long long i = first + threadIdx.x + u * kBlock;
+      if (i < end) element(i, rv[u], qv[u], [&] { return wv[u]; });
+    }
+  } else {
+    for (long long b0 = first; b0 < n; b0 += gx * chunk) {
+      const long long e = min(b0 + chunk, n);
+#pragma unroll 4
+      for (long long i = b0 + threadIdx.x; i < e; i += kBlock)
+        element(i, r[i], (double)q[i], [&] { return wdinv[(unsigned)i / 3]; });
     }
   }
   acc = block_sum(acc);
   if (threadIdx.x == 0) rr_partials[bx] = acc;
 }
-template <typename TW, typename TQ>
+template <typename TW, typename TQ, bool ONCE>
 __global__ void k_update_r_first(long long n, const double* __restrict__ pq_partials, int npq,
                                  double* __restrict__ sc, const int* __restrict__ active,
                                  const TQ* __restrict__ q, double* __restrict__ r,
                                  double* __restrict__ rr_partials, int parity, const TW* __restrict__ wdinv,
                                  float* __restrict__ f32, TW* __restrict__ t, const int* __restrict__ repl) {
-  update_r_first_block<TW, TQ>(n, pq_partials, npq, sc, active, q, r, rr_partials, parity, wdinv, f32, t, repl,
+  update_r_first_block<TW, TQ, ONCE>(n, pq_partials, npq, sc, active, q, r, rr_partials, parity, wdinv, f32, t, repl,
                                blockIdx.x, blockIdx.y);
 }
-template <typename TW, typename TQ>
+template <typename TW, typename TQ, bool ONCE>
 __global__ void k_update_r_first_batch(Batch<UpdateRTask<TW, TQ>> tb) {
   const int t = batch_task(tb.begin, tb.n, (int)blockIdx.x);
   const UpdateRTask<TW, TQ>& a = tb.a[t];
   const int local = (int)blockIdx.x - tb.begin[t];
-  update_r_first_block<TW, TQ>(a.n, a.pq_partials, a.npq, a.sc, a.active, a.q, a.r, a.rr_partials, a.parity,
+  update_r_first_block<TW, TQ, ONCE>(a.n, a.pq_partials, a.npq, a.sc, a.active, a.q, a.r, a.rr_partials, a.parity,
                                a.wdinv, a.f32, a.t, a.repl, local % kReduceBlocks, local / kReduceBlocks);
 }
 
@@ -665,13 +703,14 @@ __global__ void k_update_r_first_batch(Batch<UpdateRTask<TW, TQ>> tb) {
 // copy.  A right-hand side that has stopped only republishes its scalars.
 __device__ __forceinline__ void rr_check_block(const double* __restrict__ rr_partials, double* __restrict__ sc,
                                                int* __restrict__ active, double* __restrict__ host_slot, int rhs) {
-  const double rr = sum_partials(rr_partials + (long long)kReduceBlocks * rhs);
-  if (threadIdx.x != 0) return;
   double* s = sc + kScalars * rhs;
   double v[kScalars];
 #pragma unroll
   for (int j = 0; j < kScalars; ++j) v[j] = s[j];
-  if (active[rhs]) {
+  const int was_active = active[rhs];
+  const double rr = sum_partials(rr_partials + (long long)kReduceBlocks * rhs);
+  if (threadIdx.x != 0) return;
+  if (was_active) {
     v[kRr] = rr;
     v[kIts] += 1.0;
     const bool finite = rr == rr && rr < 1e308;
@@ -709,95 +748,114 @@ __global__ void k_rr_check_batch(Batch<RrCheckTask> tb) {
 // binary32 V-cycle output widened on the fly.
 // The x update is skipped when s[kXPend] is 0 (a residual replacement has
 // already applied it); p32 (may be null) receives a binary32 copy of the new p.
-template <typename TZ>
-__device__ __forceinline__ void update_px_block(long long n, const double* __restrict__ rz_partials, int nrz,
-                                                double* __restrict__ sc, const int* __restrict__ active,
-                                                const TZ* __restrict__ z, double* __restrict__ p,
-                                                double* __restrict__ x, int parity, float* __restrict__ p32,
-                                                float* __restrict__ p32b, int bx, int rhs) {
+// What the pass does with x and the direction: p in binary64 (its x += alpha p), p
+// also copied to p32, or p in binary32 only: p_k of iteration k in p32 (k odd)
+// or p32b (k even).  After an odd k (kPxOdd): p_(k+1) = z + beta p_k into p32b.
+// After an even k (kPxEven): x += alpha_(k-1) p_(k-1) (p32), x += alpha_k p_k
+// (p32b), and p_(k+1) = z + beta p_k into p32, over p_(k-1).
+enum PxForm { kPxDouble, kPxCopied, kPxOdd, kPxEven };
+// FRESH: x has not been written yet and counts as zero.
+template <typename TZ, bool ONCE, int FORM, bool FRESH>
+__device__ __forceinline__ void update_px_form(long long n, const double* __restrict__ rz_partials, int nrz,
+                                               double* __restrict__ sc, const int* __restrict__ active,
+                                               const TZ* __restrict__ z, double* __restrict__ p,
+                                               double* __restrict__ x, int parity, float* __restrict__ p32,
+                                               float* __restrict__ p32b, int bx, int rhs) {
   constexpr int gx = kReduceBlocks;
-  if (!active[rhs]) return;
-  const long long chunk = vec_chunk(n);
-  double rzs = 0.0;
-  for (int i = threadIdx.x; i < nrz; i += kBlock) rzs += rz_partials[(long long)nrz * rhs + i];
-  const double rz = block_sum_all(rzs);
+  constexpr bool kX = FORM != kPxOdd, kWide = FORM == kPxDouble || FORM == kPxCopied;
+  const long long chunk = vec_chunk(n), first = bx * chunk, end = min(first + chunk, n);
+  if (first >= n || (!ONCE && !active[rhs])) return;
+  const long long off = n * rhs;
+  z += off;
+  x += off;
+  if (kWide) p += off;
+  if (FORM != kPxDouble) p32 += off;
+  if (!kWide) p32b += off;
+  struct In {
+    double z, p, odd, x;
+  };
+  auto load = [&](long long i) {
+    return In{(double)z[i], kWide ? p[i] : (double)(FORM == kPxOdd ? p32 : p32b)[i],
+              FORM == kPxEven ? (double)p32[i] : 0.0, kX && !FRESH ? x[i] : 0.0};
+  };
+  In in[kVecAhead];
+  if constexpr (ONCE) {
+#pragma unroll
+    for (int u = 0; u < kVecAhead; ++u) {
+      const long long i = first + threadIdx.x + u * kBlock;
+      if (i < end) in[u] = load(i);
+    }
+  }
   double* s = sc + kScalars * rhs;
-  const double beta = rz / s[kRz0 + parity];
-  const double alpha = s[kXPend] != 0.0 ? s[kAlpha] : 0.0;
+  const int act = active[rhs];
+  const double rz0 = s[kRz0 + parity], pend = s[kXPend], al = s[kAlpha];
+  const double a_odd = s[kAlphaP], a_even = s[kAlphaP + 1];
+  const double rz = block_sum_all(strided_sum(rz_partials + (long long)nrz * rhs, nrz));
+  if (!act) return;
+  const double alpha = pend != 0.0 ? al : 0.0, beta = rz / rz0;
   if (bx == 0 && threadIdx.x == 0) {
     s[kRz0 + 1 - parity] = rz;
     s[kBeta] = beta;
   }
-  const long long off = n * rhs;
-  z += off;
-  x += off;
-  if (p32) p32 += off;
-  if (!p) {
-    // The direction is held in binary32 only, p_k of iteration k in p32 (k odd)
-    // or p32b (k even); parity = (k - 1) & 1.  After an odd k: p_(k+1) = z +
-    // beta p_k into p32b.  After an even k: x += alpha_(k-1) p_(k-1) (p32), x +=
-    // alpha_k p_k (p32b), and p_(k+1) = z + beta p_k into p32, over p_(k-1).
-    p32b += off;
-    if (parity) {
-      const double a_odd = s[kAlphaP], a_even = s[kAlphaP + 1];
-      const bool fresh = s[kIts] == 2.0;  // x has not been written yet
-      for (long long b0 = bx * chunk; b0 < n; b0 += gx * chunk) {
-        const long long e = min(b0 + chunk, n);
-#pragma unroll 4
-        for (long long i = b0 + threadIdx.x; i < e; i += kBlock) {
-          const double po = (double)p32[i], pe = (double)p32b[i];
-          double xi = fresh ? 0.0 : x[i];
-          xi += a_odd * po;
-          xi += a_even * pe;
-          x[i] = xi;
-          p32[i] = (float)((double)z[i] + beta * pe);
-        }
-      }
+  auto element = [&](long long i, const In& v) {
+    const double pn = v.z + beta * v.p;
+    if (kWide) {
+      x[i] = v.x + alpha * v.p;
+      p[i] = pn;
+      if (FORM == kPxCopied) p32[i] = (float)pn;
+    } else if (FORM == kPxEven) {
+      double xn = v.x + a_odd * v.odd;
+      xn += a_even * v.p;
+      x[i] = xn;
+      p32[i] = (float)pn;
     } else {
-      for (long long b0 = bx * chunk; b0 < n; b0 += gx * chunk) {
-        const long long e = min(b0 + chunk, n);
-#pragma unroll 4
-        for (long long i = b0 + threadIdx.x; i < e; i += kBlock)
-          p32b[i] = (float)((double)z[i] + beta * (double)p32[i]);
-      }
+      p32b[i] = (float)pn;
     }
-    return;
-  }
-  p += off;
-  const bool fresh = !p32 && s[kIts] == 1.0;  // x has not been written yet
-  for (long long b0 = bx * chunk; b0 < n; b0 += gx * chunk) {
-    const long long e = min(b0 + chunk, n);
-    if (p32) {
+  };
+  if constexpr (ONCE) {
+#pragma unroll
+    for (int u = 0; u < kVecAhead; ++u) {
+      const long long i = first + threadIdx.x + u * kBlock;
+      if (i < end) element(i, in[u]);
+    }
+  } else {
+    for (long long b0 = first; b0 < n; b0 += gx * chunk) {
+      const long long e = min(b0 + chunk, n);
 #pragma unroll 4
-      for (long long i = b0 + threadIdx.x; i < e; i += kBlock) {
-        const double pi = p[i];
-        x[i] += alpha * pi;
-        const double pn = (double)z[i] + beta * pi;
-        p[i] = pn;
-        p32[i] = (float)pn;
-      }
-    } else {
-#pragma unroll 4
-      for (long long i = b0 + threadIdx.x; i < e; i += kBlock) {
-        const double pi = p[i];
-        x[i] = (fresh ? 0.0 : x[i]) + alpha * pi;
-        p[i] = (double)z[i] + beta * pi;
-      }
+      for (long long i = b0 + threadIdx.x; i < e; i += kBlock) element(i, load(i));
     }
   }
 }
-template <typename TZ>
+template <typename TZ, bool ONCE>
+__device__ __forceinline__ void update_px_block(long long n, const double* rz_partials, int nrz, double* sc,
+                                                const int* active, const TZ* z, double* p, double* x, int parity,
+                                                int fresh, float* p32, float* p32b, int bx, int rhs) {
+  if (p && p32)
+    update_px_form<TZ, ONCE, kPxCopied, false>(n, rz_partials, nrz, sc, active, z, p, x, parity, p32, p32b, bx, rhs);
+  else if (p && fresh)
+    update_px_form<TZ, ONCE, kPxDouble, true>(n, rz_partials, nrz, sc, active, z, p, x, parity, p32, p32b, bx, rhs);
+  else if (p)
+    update_px_form<TZ, ONCE, kPxDouble, false>(n, rz_partials, nrz, sc, active, z, p, x, parity, p32, p32b, bx, rhs);
+  else if (!parity)
+    update_px_form<TZ, ONCE, kPxOdd, false>(n, rz_partials, nrz, sc, active, z, p, x, parity, p32, p32b, bx, rhs);
+  else if (fresh)
+    update_px_form<TZ, ONCE, kPxEven, true>(n, rz_partials, nrz, sc, active, z, p, x, parity, p32, p32b, bx, rhs);
+  else
+    update_px_form<TZ, ONCE, kPxEven, false>(n, rz_partials, nrz, sc, active, z, p, x, parity, p32, p32b, bx, rhs);
+}
+template <typename TZ, bool ONCE>
 __global__ void k_update_px(long long n, const double* __restrict__ rz_partials, int nrz, double* __restrict__ sc,
                             const int* __restrict__ active, const TZ* __restrict__ z, double* __restrict__ p,
-                            double* __restrict__ x, int parity, float* __restrict__ p32, float* __restrict__ p32b) {
-  update_px_block<TZ>(n, rz_partials, nrz, sc, active, z, p, x, parity, p32, p32b, blockIdx.x, blockIdx.y);
+                            double* __restrict__ x, int parity, int fresh, float* __restrict__ p32,
+                            float* __restrict__ p32b) {
+  update_px_block<TZ, ONCE>(n, rz_partials, nrz, sc, active, z, p, x, parity, fresh, p32, p32b, blockIdx.x, blockIdx.y);
 }
-template <typename TZ>
+template <typename TZ, bool ONCE>
 __global__ void k_update_px_batch(Batch<UpdatePxTask<TZ>> tb) {
   const int t = batch_task(tb.begin, tb.n, (int)blockIdx.x);
   const UpdatePxTask<TZ>& a = tb.a[t];
   const int local = (int)blockIdx.x - tb.begin[t];
-  update_px_block<TZ>(a.n, a.rz_partials, a.nrz, a.sc, a.active, a.z, a.p, a.x, a.parity, a.p32, a.p32b,
+  update_px_block<TZ, ONCE>(a.n, a.rz_partials, a.nrz, a.sc, a.active, a.z, a.p, a.x, a.parity, a.fresh, a.p32, a.p32b,
                       local % kReduceBlocks, local / kReduceBlocks);
 }
 
@@ -1094,8 +1152,9 @@ template <typename TW, typename TQ>
 void launch_update_r_first(long long n, const double* pq_partials, int npq, double* sc, const int* active,
                            const TQ* q, double* r, double* rr_partials, int parity, const TW* wdinv, float* f32,
                            TW* t, int nrhs, hipStream_t s, const int* repl) {
-  k_update_r_first<TW, TQ><<<dim3(kReduceBlocks, nrhs), kBlock, 0, s>>>(n, pq_partials, npq, sc, active, q, r,
-                                                                         rr_partials, parity, wdinv, f32, t, repl);
+  auto* k = vec_once(n) ? k_update_r_first<TW, TQ, true> : k_update_r_first<TW, TQ, false>;
+  k<<<dim3(kReduceBlocks, nrhs), kBlock, 0, s>>>(n, pq_partials, npq, sc, active, q, r, rr_partials, parity, wdinv,
+                                                 f32, t, repl);
 }
 template void launch_update_r_first<double, double>(long long, const double*, int, double*, const int*,
                                                     const double*, double*, double*, int, const double*, float*,
@@ -1124,14 +1183,15 @@ void launch_rr_check(const double* rr_partials, double* sc, int* active, double*
 }
 template <typename TZ>
 void launch_update_px(long long n, const double* rz_partials, int nrz, double* sc, const int* active, const TZ* z,
-                      double* p, double* x, int parity, int nrhs, hipStream_t s, float* p32, float* p32b) {
-  k_update_px<TZ><<<dim3(kReduceBlocks, nrhs), kBlock, 0, s>>>(n, rz_partials, nrz, sc, active, z, p, x, parity,
-                                                                p32, p32b);
+                      double* p, double* x, int parity, int fresh, int nrhs, hipStream_t s, float* p32,
+                      float* p32b) {
+  auto* k = vec_once(n) ? k_update_px<TZ, true> : k_update_px<TZ, false>;
+  k<<<dim3(kReduceBlocks, nrhs), kBlock, 0, s>>>(n, rz_partials, nrz, sc, active, z, p, x, parity, fresh, p32, p32b);
 }
 template void launch_update_px<double>(long long, const double*, int, double*, const int*, const double*, double*,
-                                       double*, int, int, hipStream_t, float*, float*);
+                                       double*, int, int, int, hipStream_t, float*, float*);
 template void launch_update_px<float>(long long, const double*, int, double*, const int*, const float*, double*,
-                                      double*, int, int, hipStream_t, float*, float*);
+                                      double*, int, int, int, hipStream_t, float*, float*);
 void launch_flush_x(long long n, const double* sc, const double* p, double* x, int nrhs, hipStream_t s,
                     const int* act, const float* p32, const float* p32b, bool cleared) {
   if (p)
@@ -1187,7 +1247,8 @@ template void launch_coarse_gemv_batch<double>(const Batch<GemvTask<double>>&, h
 
 template <typename TW, typename TQ>
 void launch_update_r_first_batch(const Batch<UpdateRTask<TW, TQ>>& b, hipStream_t s) {
-  k_update_r_first_batch<TW, TQ><<<b.begin[b.n], kBlock, 0, s>>>(b);
+  auto* k = vec_once(b.a[0].n) ? k_update_r_first_batch<TW, TQ, true> : k_update_r_first_batch<TW, TQ, false>;
+  k<<<b.begin[b.n], kBlock, 0, s>>>(b);
 }
 template void launch_update_r_first_batch<double, double>(const Batch<UpdateRTask<double, double>>&, hipStream_t);
 template void launch_update_r_first_batch<float, double>(const Batch<UpdateRTask<float, double>>&, hipStream_t);
@@ -1199,7 +1260,8 @@ void launch_rr_check_batch(const Batch<RrCheckTask>& b, hipStream_t s) {
 
 template <typename TZ>
 void launch_update_px_batch(const Batch<UpdatePxTask<TZ>>& b, hipStream_t s) {
-  k_update_px_batch<TZ><<<b.begin[b.n], kBlock, 0, s>>>(b);
+  auto* k = vec_once(b.a[0].n) ? k_update_px_batch<TZ, true> : k_update_px_batch<TZ, false>;
+  k<<<b.begin[b.n], kBlock, 0, s>>>(b);
 }
 template void launch_update_px_batch<double>(const Batch<UpdatePxTask<double>>&, hipStream_t);
 template void launch_update_px_batch<float>(const Batch<UpdatePxTask<float>>&, hipStream_t);
