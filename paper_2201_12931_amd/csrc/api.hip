@@ -1263,7 +1263,8 @@ int hexmg_set_density(hexmg_grid_t g, const double* rho, void* stream) {
       }
       launch_coarse_assemble(C, g->Ke64, Ec, g->Acoarse, a);
     }
-    launch_spd_inverse(nc, g->Acoarse, g->inv_scratch, a);
+    // a node couples to its 26 neighbours
+    launch_spd_inverse(nc, 3 * (1 + C.nxn + C.nxn * C.nyn) + 2, g->Acoarse, g->inv_scratch, a);
     HIP_TRY(hipEventRecord(g->ev_coarse, a));
     g->coarse_pending = true;
     g->coarse_waited_valid = false;

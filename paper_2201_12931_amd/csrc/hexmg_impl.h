@@ -440,10 +440,11 @@ void launch_to64_dot(long long n, const float* u32, const double* r, double* z, 
                      const int* act, hipStream_t s);
 void launch_f64_to_f32(long long n, const double* a, float* b, int nrhs, const int* act, hipStream_t s);
 
-// Inverse of the n x n SPD row-major A in place, by block sweeps (inverse.hip);
-// scratch: spd_inverse_scratch(n) doubles.  2 + ceil(n/64) launches.
+// Inverse of the n x n SPD row-major A in place, by block sweeps (inverse.hip); A_ij
+// is zero for |i - j| > band.  scratch: spd_inverse_scratch(n) doubles.  Up to 2 +
+// ceil(n/64) launches, fewer with a band.
 size_t spd_inverse_scratch(int n);
-void launch_spd_inverse(int n, double* A, double* scratch, hipStream_t s);
+void launch_spd_inverse(int n, int band, double* A, double* scratch, hipStream_t s);
 
 // Density filter and optimality criteria (topopt.hip)
 void launch_filter(int nx, int ny, int nz, double rmin, int adjoint, const double* in, double* out, double* tmp,

@@ -6,12 +6,21 @@
 // and keeps it symmetric; swept over every pivot block it is -A^-1.  The
 // diagonal blocks met on the way are SPD, so no pivoting is needed.  Only the
 // 64x64 tiles (I, J) with I >= J are kept, so a step does half the tiles of a
-// Gauss-Jordan step on the full matrix.  A step on few tiles is bound by its
-// serial chain (launch, one round of loads, two 64^3 products at the binary64
-// matrix rate, the next pivot tile's inverse: 18 us, the inverse 8 of them), one
-// on many by the products.  Measured, pack to unpack: 675 unknowns 205 us, 1911
-// 714 us, 2304 885 us (290, 1960 and 2200 us as a full Gauss-Jordan whose tiles
-// took three rounds of loads and whose pivot tile came in row order).
+// Gauss-Jordan step on the full matrix.
+//
+// The operator couples tiles up to wb apart, and sweeping pivots from the top
+// fills only the tiles up to row K + wb (from the bottom: down to row K - wb).  So
+// while K' - K > wb a step sweeps two pivots, K from the top and K' from the
+// bottom: A_KK' is still zero, and D of the two together is block diagonal.  It
+// leaves alone what neither reaches.  The last wb + 1 pivots at most are swept
+// one to a step on all tiles.
+//
+// A step on few tiles is bound by its serial chain (launch, one round of loads, two
+// 64^3 products at the binary64 matrix rate, the next pivot tile's inverse: 18 us, the
+// inverse 8 of them), one on many by the products.  Measured, pack to unpack: 675
+// unknowns (wb = 3) 143 us in 7 steps, 1911 (5) 385 us in 18, 2304 (7) 508 us in 22; in order
+// on all tiles 205, 714 and 885 us in 11, 30 and 36 steps (and 290, 1960 and 2200 us as a
+// full Gauss-Jordan whose tiles took three rounds of loads).
 //
 // Layouts.  v_mfma_f64_16x16x4f64: lane l holds the left operand's (row l%16, k
 // l/16), the right operand's (k l/16, column l%16), and of the result, value v,
@@ -152,33 +161,54 @@ __device__ inline void invert_tile(InverseLds& lds, d4 (&y)[4], double* __restri
     for (int v = 0; v < 4; ++v) D[w * 1024 + (4 * r + v) * 64 + l] = -y[r][v];
 }
 
-// What the step after a tile's last change reads of it: tiles of the next pivot
-// column K go to its panel P (operand order; of a tile (K, J) its transpose),
-// the next pivot tile's inverse to D.
-__device__ inline void hand_over(InverseLds& s, int K, int I, int J, d4 (&y)[4], double* __restrict__ P,
-                                 double* __restrict__ D) {
+// The pivots of a step: K[0] from the top and K[1] from the bottom; or K[0] alone
+// (K[1] = -1), which then reaches every tile.  Both -1: no step.
+struct Pivots {
+  int K[2];
+  __host__ __device__ int of(int side) const { return side ? K[1] : K[0]; }
+};
+// Whether a pivot of side 0 or 1 changes row (or column) block I.
+__device__ inline bool reaches(const Pivots& p, int side, int wb, int I) {
+  const int K = p.of(side);
+  return K >= 0 && (p.K[1] < 0 || (side == 0 ? I <= K + wb : I >= K - wb));
+}
+
+// What the next step (pivots q) reads of a tile after its last change: tiles of a
+// pivot column K go to its panel P (operand order; of a tile (K, J) its transpose),
+// a pivot tile's inverse to D.  Panels and inverses of side 1 follow those of side 0.
+__device__ inline void hand_over(InverseLds& s, const Pivots& q, int nt, int I, int J, d4 (&y)[4],
+                                 double* __restrict__ P, double* __restrict__ D) {
   const int l = threadIdx.x & 63, w = threadIdx.x >> 6;
-  if (I == K && J == K) {  // uniform per block
-    invert_tile(s, y, D);
-  } else if (I == K) {
-    double* p = P + (long long)J * kTile + w * 1024 + l;
+#pragma unroll 1
+  for (int side = 0; side < 2; ++side) {  // at most one side is this tile's pivot
+    const int K = q.of(side);
+    if (K < 0) continue;  // uniform per block, as is what follows
+    double* Ps = P + (long long)side * nt * kTile;
+    if (I == K && J == K) {
+      invert_tile(s, y, D + side * kTile);
+      return;
+    }
+    if (I == K) {
+      double* p = Ps + (long long)J * kTile + w * 1024 + l;
 #pragma unroll
-    for (int t = 0; t < 4; ++t)
+      for (int t = 0; t < 4; ++t)
 #pragma unroll
-      for (int v = 0; v < 4; ++v) p[(4 * t + v) * 64] = y[t][v];
-  } else if (J == K) {
-    double* p = P + (long long)I * kTile + (4 * w + ((l >> 2) & 3)) * 64 + (l & 3) * 16 + (l >> 4);
+        for (int v = 0; v < 4; ++v) p[(4 * t + v) * 64] = y[t][v];
+    } else if (J == K) {
+      double* p = Ps + (long long)I * kTile + (4 * w + ((l >> 2) & 3)) * 64 + (l & 3) * 16 + (l >> 4);
 #pragma unroll
-    for (int t = 0; t < 4; ++t)
+      for (int t = 0; t < 4; ++t)
 #pragma unroll
-      for (int v = 0; v < 4; ++v) p[t * 1024 + 4 * v] = y[t][v];
+        for (int v = 0; v < 4; ++v) p[t * 1024 + 4 * v] = y[t][v];
+    }
   }
 }
 
 // The lower triangle of the row-major A (n x n) as tiles, padded by the identity
-// to whole tiles; the panel and pivot inverse of step 0.  One block per tile.
-__global__ __launch_bounds__(kBlock) void k_sweep_pack(int n, const double* __restrict__ A, double* __restrict__ T,
-                                                       double* __restrict__ P, double* __restrict__ D) {
+// to whole tiles; the panels and pivot inverses of the first step (q).  One block per tile.
+__global__ __launch_bounds__(kBlock) void k_sweep_pack(int n, int nt, Pivots q, const double* __restrict__ A,
+                                                       double* __restrict__ T, double* __restrict__ P,
+                                                       double* __restrict__ D) {
   __shared__ InverseLds lds;
   int I = 0;
   const int b = blockIdx.x;
@@ -198,37 +228,23 @@ __global__ __launch_bounds__(kBlock) void k_sweep_pack(int n, const double* __re
   for (int t = 0; t < 4; ++t)
 #pragma unroll
     for (int v = 0; v < 4; ++v) tile[(4 * t + v) * 64] = y[t][v];
-  hand_over(lds, 0, I, J, y, P, D);
+  hand_over(lds, q, nt, I, J, y, P, D);
 }
 
-// Sweep of pivot block K, one block per tile (I, J), I >= J, in place (a tile is
-// read and written by its own block only; the pivot column is read from the
-// panel P that the previous step left).  Block 0 takes the next pivot tile: its
-// inverse is the serial part of the step (every other block needs it in the next
-// one) and so starts first and runs beside the other tiles.
-__global__ __launch_bounds__(kBlock) void k_sweep_step(int nt, int K, double* __restrict__ T,
-                                                       const double* __restrict__ P, const double* __restrict__ D,
-                                                       double* __restrict__ Pn, double* __restrict__ Dn) {
-  __shared__ union Lds {
-    double op[2][kTile];  // D and A_IK in operand order
-    InverseLds inv;
-    __device__ Lds() {}
-  } lds;
-  const int last = K + 1 < nt ? (K + 1) * (K + 2) / 2 + K + 1 : 0;  // the next pivot tile's place in row order
-  int b = blockIdx.x;
-  b = b == 0 ? last : (b <= last ? b - 1 : b);
-  int I = (int)((sqrtf(8.0f * (float)b + 1.0f) - 1.0f) * 0.5f);
-  while ((I + 1) * (I + 2) / 2 <= b) ++I;
-  while (I * (I + 1) / 2 > b) --I;
-  const int J = b - I * (I + 1) / 2;
+struct SweepOperands {
+  double op[2][kTile];  // D and A_IK in operand order
+};
+
+// The change of the tile (I, J), I >= J, by the pivot K: y <- y - A_IK D A_KJ, or
+// (I = K or J = K) y <- its new value.  P: the pivot column's panel.
+__device__ __forceinline__ void sweep_tile(SweepOperands& lds, int K, int I, int J, const double* __restrict__ P,
+                                           const double* __restrict__ D, d4 (&y)[4]) {
   const int l = threadIdx.x & 63, w = threadIdx.x >> 6;
-  double* tile = T + tri(I, J) + w * 1024 + l;
-  d4 y[4];
   if (I == K && J == K) {  // -D: row-major position (r, c) of the symmetric D in operand order
 #pragma unroll
     for (int t = 0; t < 4; ++t)
 #pragma unroll
-      for (int v = 0; v < 4; ++v) tile[(4 * t + v) * 64] = -D[w * 1024 + (4 * t + v) * 64 + l];
+      for (int v = 0; v < 4; ++v) y[t][v] = -D[w * 1024 + (4 * t + v) * 64 + l];
     return;
   }
   // every global load is issued before the first use
@@ -247,10 +263,10 @@ __global__ __launch_bounds__(kBlock) void k_sweep_step(int nt, int K, double* __
 #pragma unroll
     for (int m = 0; m < kPairs; ++m) vi[m] = gi[m * kBlock];
   }
+  if (I == K || J == K) {
 #pragma unroll
-  for (int t = 0; t < 4; ++t)
-#pragma unroll
-    for (int v = 0; v < 4; ++v) y[t][v] = (I == K || J == K) ? 0.0 : tile[(4 * t + v) * 64];
+    for (int t = 0; t < 4; ++t) y[t] = d4{0.0, 0.0, 0.0, 0.0};
+  }
   if (J != K) {
 #pragma unroll
     for (int m = 0; m < kPairs; ++m) ((d2*)lds.op[0])[threadIdx.x + m * kBlock] = vd[m];
@@ -284,13 +300,70 @@ __global__ __launch_bounds__(kBlock) void k_sweep_step(int nt, int K, double* __
         y[t] = __builtin_amdgcn_mfma_f64_16x16x4f64(lds.op[1][t * 1024 + ks * 64 + l], -x[ks >> 2][ks & 3], y[t], 0,
                                                     0, 0);
   }
+}
+
+// Sweep of the pivots p, one block per tile (I, J), I >= J, in place (a tile is
+// read and written by its own block only; the pivot columns are read from the
+// panels P that the previous step left), and what the next step (pivots q) reads
+// of the tiles that it reaches.  The first blocks take the next pivot tiles: their
+// inverses are the serial part of the step (every other block needs them in the next
+// one) and so start first and run beside the other tiles.
+__global__ __launch_bounds__(kBlock) void k_sweep_step(int nt, int wb, Pivots p, Pivots q, double* __restrict__ T,
+                                                       const double* __restrict__ P, const double* __restrict__ D,
+                                                       double* __restrict__ Pn, double* __restrict__ Dn) {
+  __shared__ union Lds {
+    SweepOperands op;
+    InverseLds inv;
+    __device__ Lds() {}
+  } lds;
+  int b = blockIdx.x;
+  if (q.K[0] >= 0) {  // the next pivot tiles' places in row order, the first of them before the second
+    const int p0 = q.K[0] * (q.K[0] + 3) / 2, p1 = q.K[1] >= 0 ? q.K[1] * (q.K[1] + 3) / 2 : -1;
+    if (b == 0) {
+      b = p0;
+    } else if (p1 < 0) {
+      b = b <= p0 ? b - 1 : b;
+    } else if (b == 1) {
+      b = p1;
+    } else {
+      b = b - 2 < p0 ? b - 2 : (b - 1 < p1 ? b - 1 : b);
+    }
+  }
+  int I = (int)((sqrtf(8.0f * (float)b + 1.0f) - 1.0f) * 0.5f);
+  while ((I + 1) * (I + 2) / 2 <= b) ++I;
+  while (I * (I + 1) / 2 > b) --I;
+  const int J = b - I * (I + 1) / 2;
+  bool change = false, hand = false;  // uniform per block
+#pragma unroll
+  for (int side = 0; side < 2; ++side) {
+    change = change || (reaches(p, side, wb, I) && reaches(p, side, wb, J));
+    hand = hand || ((I == q.of(side) || J == q.of(side)) && reaches(q, side, wb, I) && reaches(q, side, wb, J));
+  }
+  if (!change && !hand) return;
+  const int l = threadIdx.x & 63, w = threadIdx.x >> 6;
+  double* tile = T + tri(I, J) + w * 1024 + l;
+  d4 y[4];
 #pragma unroll
   for (int t = 0; t < 4; ++t)
 #pragma unroll
-    for (int v = 0; v < 4; ++v) tile[(4 * t + v) * 64] = y[t][v];
-  if (K + 1 < nt) {
-    if (I == K + 1 && J == K + 1) __syncthreads();  // the operands' readers are done with the LDS
-    hand_over(lds.inv, K + 1, I, J, y, Pn, Dn);
+    for (int v = 0; v < 4; ++v) y[t][v] = tile[(4 * t + v) * 64];
+  bool used = false;
+#pragma unroll 1
+  for (int side = 0; side < 2; ++side) {
+    if (!(reaches(p, side, wb, I) && reaches(p, side, wb, J))) continue;
+    if (used) __syncthreads();  // the operands' readers are done with the LDS
+    sweep_tile(lds.op, p.of(side), I, J, P + (long long)side * nt * kTile, D + side * kTile, y);
+    used = true;
+  }
+  if (change) {
+#pragma unroll
+    for (int t = 0; t < 4; ++t)
+#pragma unroll
+      for (int v = 0; v < 4; ++v) tile[(4 * t + v) * 64] = y[t][v];
+  }
+  if (hand) {
+    if (used && I == J) __syncthreads();  // as above, before a pivot tile's inverse
+    hand_over(lds.inv, q, nt, I, J, y, Pn, Dn);
   }
 }
 
@@ -323,17 +396,30 @@ __global__ __launch_bounds__(kBlock) void k_sweep_unpack(int n, const double* __
 
 size_t spd_inverse_scratch(int n) {
   const long long nt = (n + kGJBlock - 1) / kGJBlock;
-  return (size_t)(tri((int)nt, 0) + (2 * nt + 2) * kTile);
+  return (size_t)(tri((int)nt, 0) + 2 * (2 * nt + 2) * kTile);
 }
 
-void launch_spd_inverse(int n, double* A, double* scratch, hipStream_t s) {
+void launch_spd_inverse(int n, int band, double* A, double* scratch, hipStream_t s) {
   const int nt = (n + kGJBlock - 1) / kGJBlock, tiles = nt * (nt + 1) / 2;
+  const int wb = (band + kGJBlock - 1) / kGJBlock;
   double* T = scratch;
-  double* P[2] = {T + tri(nt, 0), T + tri(nt, 0) + (long long)nt * kTile};
-  double* D[2] = {P[1] + (long long)nt * kTile, P[1] + (long long)(nt + 1) * kTile};
-  k_sweep_pack<<<tiles, kBlock, 0, s>>>(n, A, T, P[0], D[0]);
-  for (int k = 0; k < nt; ++k)
-    k_sweep_step<<<tiles, kBlock, 0, s>>>(nt, k, T, P[k & 1], D[k & 1], P[(k + 1) & 1], D[(k + 1) & 1]);
+  double* P[2] = {T + tri(nt, 0), T + tri(nt, 0) + 2ll * nt * kTile};  // by parity, then side
+  double* D[2] = {P[1] + 2ll * nt * kTile, P[1] + (2ll * nt + 2) * kTile};
+  // pivots from both ends while they are not coupled, then the rest in order
+  auto next = [&](int lo, int hi) {  // lo..hi are left
+    Pivots p{{lo <= hi ? lo : -1, hi - lo > wb ? hi : -1}};
+    return p;
+  };
+  int lo = 0, hi = nt - 1;
+  Pivots p = next(lo, hi);
+  k_sweep_pack<<<tiles, kBlock, 0, s>>>(n, nt, p, A, T, P[0], D[0]);
+  for (int k = 0; p.K[0] >= 0; ++k) {
+    ++lo;
+    if (p.K[1] >= 0) --hi;
+    const Pivots q = next(lo, hi);
+    k_sweep_step<<<tiles, kBlock, 0, s>>>(nt, wb, p, q, T, P[k & 1], D[k & 1], P[(k + 1) & 1], D[(k + 1) & 1]);
+    p = q;
+  }
   k_sweep_unpack<<<tiles, kBlock, 0, s>>>(n, T, A);
 }
 
