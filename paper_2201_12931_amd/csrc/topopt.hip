@@ -294,9 +294,11 @@ __device__ inline double oc_point(double lo, double hi, int p) { return lo + (hi
 // sum_e dv_e x_new_e(lambda_p).  The block's sums over its 64 lanes are taken for
 // all points at once: in each of five exchanges a lane hands half of its points to its
 // partner and keeps the other half, so 32 exchanges do what 32 separate sums do
-// in 192.  One pass at 256x128x128 takes 35 us (100 MB read, 2.9 TB/s beside 32
-// products and clamps per element; 72 us with pow for
-// the square root).
+// in 192.  One pass at 256x128x128 takes 33 us (100 MB read, beside the square root, the
+// division and 32 products, clamps and sums per element in binary64), 72 with pow
+// for the square root; at 120x56x40 8.6 us (10.9 with one element per thread).
+// SQRT: eta = 1/2, without pow's registers (94 instead of 149).
+template <bool SQRT>
 __global__ __launch_bounds__(kBlock) void k_oc_probe(long long n, const double* __restrict__ x,
                                                      const double* __restrict__ dc, const double* __restrict__ dv,
                                                      double eta, double move, const OcState* __restrict__ st,
@@ -314,13 +316,32 @@ __global__ __launch_bounds__(kBlock) void k_oc_probe(long long n, const double* 
     lp[p] = __longlong_as_double(((long long)__builtin_amdgcn_readfirstlane((int)(b >> 32)) << 32) |
                                  (unsigned)__builtin_amdgcn_readfirstlane((int)(unsigned)b));
   }
-  for (long long e = (long long)blockIdx.x * kBlock + threadIdx.x; e < n; e += (long long)gridDim.x * kBlock) {
-    const double xe = x[e], ve = dv[e];
-    const double se = oc_factor(xe, dc[e], ve, eta);
-    const double lo = fmax(0.0, xe - move), hi = fmin(1.0, xe + move);
-    if (ve == 0.0) continue;  // outside the volume constraint (passive)
+  // the next element is requested before this one's 32 points are evaluated
+  const long long step = (long long)gridDim.x * kBlock;
+  long long e = (long long)blockIdx.x * kBlock + threadIdx.x;
+  double xe = 0.0, ve = 0.0, de = 0.0;
+  if (e < n) {
+    xe = x[e];
+    ve = dv[e];
+    de = dc[e];
+  }
+  while (e < n) {
+    e += step;
+    double xnext = 0.0, vnext = 0.0, dnext = 0.0;
+    if (e < n) {
+      xnext = x[e];
+      vnext = dv[e];
+      dnext = dc[e];
+    }
+    if (ve != 0.0) {  // else outside the volume constraint (passive)
+      const double se = oc_factor(xe, de, ve, SQRT ? 0.5 : eta);
+      const double lo = fmax(0.0, xe - move), hi = fmin(1.0, xe + move);
 #pragma unroll
-    for (int p = 0; p < kOcProbes; ++p) acc[p] += ve * fmin(hi, fmax(lo, se * lp[p]));
+      for (int p = 0; p < kOcProbes; ++p) acc[p] += ve * fmin(hi, fmax(lo, se * lp[p]));
+    }
+    xe = xnext;
+    ve = vnext;
+    de = dnext;
   }
   const int w = threadIdx.x >> 6, lane = threadIdx.x & 63;
 #pragma unroll
@@ -343,7 +364,7 @@ __global__ __launch_bounds__(kBlock) void k_oc_probe(long long n, const double* 
   }
 }
 
-// One block of 1024 threads (6 us; one thread per point took 25, and the host's wait
+// One block of 1024 threads (3 to 6 us; one thread per point took 25, and the host's wait
 // for the volumes of every pass another 15): the volumes from the nb partials per point (32
 // threads per point, a fixed order), then the bracket narrowed to the points between which
 // the volume falls to volfrac.  A non-finite volume at the first point stops the
@@ -593,10 +614,16 @@ void launch_oc_update(long long n, const double* x, const double* dc, const doub
                       double move, double lo, double hi, int passes, double* xn, double* partials, OcState* st,
                       hipStream_t s) {
   const int nb = (int)std::min<long long>(kReduceBlocks, (n + kBlock - 1) / kBlock);
+  // a probe's thread takes four elements or more: its 32 sums over the block, and
+  // their partials in the next launch, cost more than an element
+  const int np = (int)std::min<long long>(kReduceBlocks, (n + 4 * kBlock - 1) / (4 * kBlock));
   k_oc_start<<<1, 1, 0, s>>>(st, lo, hi);
   for (int k = 0; k < passes; ++k) {
-    k_oc_probe<<<nb, kBlock, 0, s>>>(n, x, dc, dv, eta, move, st, partials);
-    k_oc_narrow<<<1, 1024, 0, s>>>(partials, nb, volfrac, st);
+    if (eta == 0.5)
+      k_oc_probe<true><<<np, kBlock, 0, s>>>(n, x, dc, dv, eta, move, st, partials);
+    else
+      k_oc_probe<false><<<np, kBlock, 0, s>>>(n, x, dc, dv, eta, move, st, partials);
+    k_oc_narrow<<<1, 1024, 0, s>>>(partials, np, volfrac, st);
   }
   k_oc_apply<<<nb, kBlock, 0, s>>>(n, x, dc, dv, eta, move, st, xn, partials);
   k_oc_finish<<<1, kBlock, 0, s>>>(partials, nb, st);
