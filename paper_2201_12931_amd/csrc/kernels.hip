@@ -57,6 +57,17 @@ __device__ inline double sum_partials(const double* __restrict__ partials) {
 
 inline int blocks_for(long long n) { return (int)((n + kBlock - 1) / kBlock); }
 
+// The per-iteration CG vector passes: each of the kReduceBlocks workgroups
+// walks contiguous ranges of vec_chunk(n) elements, kReduceBlocks ranges apart
+// (measured faster than an element-wise grid stride at the same launch).  At
+// most 4096 elements, and as many as give every workgroup the same number of
+// ranges: with 4096 throughout, 28 k unknowns kept 7 of the 1024 workgroups busy
+// and 12.8 M left a last round on 6% of them.
+__device__ inline long long vec_chunk(long long n) {
+  const unsigned m = (unsigned)n, rounds = (m + (kReduceBlocks * 4096u - 1)) / (kReduceBlocks * 4096u);
+  const unsigned ranges = kReduceBlocks * rounds;
+  return ((m + ranges - 1) / ranges + kBlock - 1) / kBlock * kBlock;
+}
 // rho^p of the SIMP law (Eq. 2): the paper's p = 3 (and p = 1) by products,
 // other exponents by pow
 __device__ inline double simp_pow(double r, double p) {
@@ -210,13 +221,23 @@ __global__ void k_simp(int ne, const double* __restrict__ rho, double E0, double
                        double scale, double* __restrict__ E64, float* __restrict__ E32,
                        double* __restrict__ rho_copy, int* __restrict__ flags) {
   int bad = 0;
-  for (int e = blockIdx.x * kBlock + threadIdx.x; e < ne; e += gridDim.x * kBlock) {
+  auto element = [&](int e, auto power) {
     const double r = rho[e];
     if (!(r >= 0.0 && r <= 1.0)) bad = 1;  // also catches NaN
     rho_copy[e] = r;
-    const double E = scale * (Emin + simp_pow(r, p) * (E0 - Emin));
+    const double E = scale * (Emin + power(r) * (E0 - Emin));
     E64[e] = E;
     E32[e] = (float)E;
+  };
+  const long long chunk = vec_chunk(ne);
+  for (long long b0 = blockIdx.x * chunk; b0 < ne; b0 += kReduceBlocks * chunk) {
+    const int e1 = (int)min(b0 + chunk, (long long)ne);
+    if (p == 3.0) {  // the usual exponent without pow's registers and branches
+#pragma unroll 4
+      for (int e = (int)b0 + threadIdx.x; e < e1; e += kBlock) element(e, [](double r) { return r * r * r; });
+    } else {
+      for (int e = (int)b0 + threadIdx.x; e < e1; e += kBlock) element(e, [&](double r) { return simp_pow(r, p); });
+    }
   }
   bad = __syncthreads_or(bad);
   if (threadIdx.x == 0) flags[blockIdx.x] = bad;
@@ -293,20 +314,26 @@ __global__ void k_modulus_from_mean(Level F, Level C, const double* __restrict__
 // L.omega where the sweep is applied).  One value per node instead of three takes
 // 8 (16) of a binary32 (binary64) sweep's 53 (106) bytes per node away: the level-0 sweeps
 // are bound by their bytes, and the solve at 768x384x384 went from 128.4 to 123.2
-// ms, the binary64 one at 256x128x128 from 11.50 to 11.09.
+// ms, the binary64 one at 256x128x128 from 11.50 to 11.09.  The eight moduli are
+// requested together: 0.63 ms at 768x384x384, 0.97 as eight loads each behind its own test.
 __global__ void k_diag(Level L, const double* __restrict__ Ke, const double* __restrict__ E,
                        double* __restrict__ wd64, float* __restrict__ wd32) {
   const int n = blockIdx.x * kBlock + threadIdx.x;
   if (n >= L.nn) return;
   int i, j, k;
   node_coords(L, n, i, j, k);
-  double d = 0;
+  double v[8];  // all eight requested before the first is added
+#pragma unroll
   for (int a = 0; a < 8; ++a) {
-    const int ax = a & 1, ay = (a >> 1) & 1, az = a >> 2;
-    const int ei = i - ax, ej = j - ay, ek = k - az;
-    if (ei < 0 || ei >= L.nx || ej < 0 || ej >= L.ny || ek < 0 || ek >= L.nz) continue;
-    d += E[ei + L.nx * (ej + L.ny * ek)] * Ke[0];
+    const int ei = i - (a & 1), ej = j - ((a >> 1) & 1), ek = k - (a >> 2);
+    const bool in = ei >= 0 && ei < L.nx && ej >= 0 && ej < L.ny && ek >= 0 && ek < L.nz;
+    v[a] = E[in ? ei + L.nx * (ej + L.ny * ek) : 0];
+    v[a] = in ? v[a] : 0.0;
   }
+  const double k0 = Ke[0];
+  double d = 0.0;
+#pragma unroll
+  for (int a = 0; a < 8; ++a) d += v[a] * k0;
   const double w = L.omega / d;
   if (wd64) wd64[n] = w;  // either output may be absent (the grid holds one precision)
   if (wd32) wd32[n] = (float)w;
@@ -411,17 +438,6 @@ __global__ void k_reduce_final(const double* __restrict__ partials, double* __re
 // of 1024 threads with eight independent chains each keeps enough loads in
 // flight that the ~70 k partials of a large level take a few microseconds.
 constexpr int kSumThreads = 1024;
-// The per-iteration CG vector passes: each of the kReduceBlocks workgroups
-// walks contiguous ranges of vec_chunk(n) elements, kReduceBlocks ranges apart
-// (measured faster than an element-wise grid stride at the same launch).  At
-// most 4096 elements, and as many as give every workgroup the same number of
-// ranges: with 4096 throughout, 28 k unknowns kept 7 of the 1024 workgroups busy
-// and 12.8 M left a last round on 6% of them.
-__device__ inline long long vec_chunk(long long n) {
-  const unsigned m = (unsigned)n, rounds = (m + (kReduceBlocks * 4096u - 1)) / (kReduceBlocks * 4096u);
-  const unsigned ranges = kReduceBlocks * rounds;
-  return ((m + ranges - 1) / ranges + kBlock - 1) / kBlock * kBlock;
-}
 // One thread's part of the sum of v[0 .. n) over a block, in a fixed order with
 // eight loads in flight.
 __device__ inline double strided_sum(const double* __restrict__ v, int n) {
@@ -468,10 +484,12 @@ __global__ __launch_bounds__(kSumThreads) void k_sum_parts(const double* __restr
 }
 
 // grid (kReduceBlocks, nrhs): r = M f (fixed DOFs zeroed), the partials of
-// ||r||^2 (the summation order of k_dot_partial), and what the first preconditioner
+// ||r||^2, and what the first preconditioner
 // reads of r: its binary32 copy f32 (mixed precision) and the first sweep from
 // zero t (either may be null).  x is not touched: the first update writes it
 // (x_zero: it is cleared here instead, for the form whose residual replacement reads it).
+// Bound by bandwidth: 1.34 ms at 768x384x384 (5.2 TB/s), 2.07 as a grid stride
+// whose load of f waited for the support bit.
 template <typename TW>
 __global__ void k_pcg_start(Level L, const double* __restrict__ f, double* __restrict__ r, double* __restrict__ x_zero,
                             double* __restrict__ partials, const TW* __restrict__ wdinv, float* __restrict__ f32,
@@ -485,19 +503,24 @@ __global__ void k_pcg_start(Level L, const double* __restrict__ f, double* __res
   if (t) t += off;
   partials += (long long)kReduceBlocks * blockIdx.y;
   double acc = 0.0;
+  const long long chunk = vec_chunk(n);
+  for (long long b0 = blockIdx.x * chunk; b0 < n; b0 += kReduceBlocks * chunk) {
+    const long long e = min(b0 + chunk, n);
 #pragma unroll 4
-  for (long long i = (long long)blockIdx.x * kBlock + threadIdx.x; i < n; i += (long long)gridDim.x * kBlock) {
-    const int node = (int)((unsigned)i / 3), c = (int)((unsigned)i % 3);
-    const double ri = ((L.mask[node] >> c) & 1) ? 0.0 : f[i];
-    r[i] = ri;
-    if (x_zero) x_zero[i] = 0.0;
-    acc += ri * ri;
-    if constexpr (sizeof(TW) == 4) {
-      const float fv = (float)ri;
-      f32[i] = fv;
-      if (t) t[i] = wdinv[node] * fv;
-    } else {
-      if (t) t[i] = wdinv[node] * ri;
+    for (long long i = b0 + threadIdx.x; i < e; i += kBlock) {
+      const int node = (int)((unsigned)i / 3), c = (int)((unsigned)i % 3);
+      const double fi = f[i];  // beside its support bit, not after it
+      const double ri = ((L.mask[node] >> c) & 1) ? 0.0 : fi;
+      r[i] = ri;
+      if (x_zero) x_zero[i] = 0.0;
+      acc += ri * ri;
+      if constexpr (sizeof(TW) == 4) {
+        const float fv = (float)ri;
+        f32[i] = fv;
+        if (t) t[i] = wdinv[node] * fv;
+      } else {
+        if (t) t[i] = wdinv[node] * ri;
+      }
     }
   }
   acc = block_sum(acc);
