@@ -129,7 +129,7 @@ __device__ __forceinline__ void first_blocks(std::integer_sequence<int, O...>, c
 // their eight children, blk += E_c G_c[a, b].  Gp holds G_c by (a, b, c) in the
 // order the unrolled loops take it (uniform indices: scalar loads).  2592
 // multiply-adds per node, below the time of writing 126 coefficients in two
-// precisions, which bounds the pass.  Level 1 of 256x128x128: 0.27 ms, and 0.23
+// precisions, which bounds the pass.  Level 1 of 256x128x128: 0.27 ms, and 0.14
 // ms for the 8450 nodes listed next to the supports (2.3 ms together as one
 // thread per block that read its moduli and supports child by child).
 __global__ __launch_bounds__(kBlock) void k_galerkin_first(Level F, Level C, const double* __restrict__ E,
@@ -155,81 +155,92 @@ __global__ __launch_bounds__(kBlock) void k_galerkin_first(Level F, Level C, con
   first_blocks(std::make_integer_sequence<int, 14>(), C, Ee, gp, m, I, J, K, S64, S32);
 }
 
-// The same at the nodes listed by k_galerkin_flag: grid (ceil(count / 64), 14).
-__global__ __launch_bounds__(64) void k_galerkin_first_masked(Level F, Level C, const double* __restrict__ E,
-                                                              const double* __restrict__ G,
-                                                              const double* __restrict__ Ke,
-                                                              const int* __restrict__ list, int count,
-                                                              double* __restrict__ S64, float* __restrict__ S32) {
-  const int t = blockIdx.x * 64 + threadIdx.x, o = 13 + blockIdx.y;
-  if (t >= count) return;
-  const int m = list[t];
+// The same at the nodes listed by k_galerkin_flag: grid (ceil(count / 64), 14).  Each
+// wave of a block takes the coarse element on one side of its 64 nodes (bits of side: above
+// the node along x, y, z), the eight are summed in that order: a chain an eighth as long
+// as a thread that walks its elements one after the other.  Two blocks to a compute unit (the
+// second launch bound) are worth the registers that they spill: 8450 nodes in 0.14
+// ms, 0.21 with one block and 0.23 with a thread per block of the stencil.
+__global__ __launch_bounds__(512, 4) void k_galerkin_first_masked(Level F, Level C, const double* __restrict__ E,
+                                                               const double* __restrict__ G,
+                                                               const double* __restrict__ Ke,
+                                                               const int* __restrict__ list, int count,
+                                                               double* __restrict__ S64, float* __restrict__ S32) {
+  __shared__ double part[8][9][64];
+  const int lane = threadIdx.x & 63, side = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int t = blockIdx.x * 64 + lane, o = 13 + blockIdx.y;
+  const int m = t < count ? list[t] : 0;
   int I, J, K;
   node_coords(C, m, I, J, K);
   const int I2 = I + off_dx(o), J2 = J + off_dy(o), K2 = K + off_dz(o);
   double blk[9] = {0, 0, 0, 0, 0, 0, 0, 0, 0};
   const bool in = I2 >= 0 && I2 < C.nxn && J2 >= 0 && J2 < C.nyn && K2 >= 0 && K2 < C.nzn;
   const int m2 = in ? I2 + C.nxn * (J2 + C.nyn * K2) : -1;
-  if (in) {
-    // coarse elements holding both nodes
-    for (int EK = (K < K2 ? K : K2) - (K == K2 ? 1 : 0); EK <= (K < K2 ? K : K2); ++EK) {
-      if (EK < 0 || EK >= C.nz) continue;
-      for (int EJ = (J < J2 ? J : J2) - (J == J2 ? 1 : 0); EJ <= (J < J2 ? J : J2); ++EJ) {
-        if (EJ < 0 || EJ >= C.ny) continue;
-        for (int EI = (I < I2 ? I : I2) - (I == I2 ? 1 : 0); EI <= (I < I2 ? I : I2); ++EI) {
-          if (EI < 0 || EI >= C.nx) continue;
-          const int ax = I - EI, ay = J - EJ, az = K - EK;  // corner of m in the coarse element
-          const int bx = I2 - EI, by = J2 - EJ, bz = K2 - EK;
-          const int a = ax + 2 * ay + 4 * az, b = bx + 2 * by + 4 * bz;
-          // the coarse element's 27 fine nodes' supports (bit q of fixed[d]: component d
-          // of node q) and its eight moduli, requested together
-          unsigned fixed[3] = {0, 0, 0};
-          double Ee[8];
+  const int EI = I - 1 + (side & 1), EJ = J - 1 + ((side >> 1) & 1), EK = K - 1 + (side >> 2);
+  // an element of the grid that holds both nodes
+  if (t < count && in && EI >= 0 && EI < C.nx && EJ >= 0 && EJ < C.ny && EK >= 0 && EK < C.nz && I2 >= EI &&
+      I2 <= EI + 1 && J2 >= EJ && J2 <= EJ + 1 && K2 >= EK && K2 <= EK + 1) {
+    // the corners of m and m2 in the coarse element, the same for the whole wave
+    const int ax = 1 - (side & 1), ay = 1 - ((side >> 1) & 1), az = 1 - (side >> 2);
+    const int bx = ax + off_dx(o), by = ay + off_dy(o), bz = az + off_dz(o);
+    const int a = ax + 2 * ay + 4 * az, b = bx + 2 * by + 4 * bz;
+    // the coarse element's 27 fine nodes' supports (bit q of fixed[d]: component d
+    // of node q) and its eight moduli, requested together
+    unsigned fixed[3] = {0, 0, 0};
 #pragma unroll
-          for (int q = 0; q < 27; ++q) {
-            const unsigned mk = F.mask[(2 * EI + q % 3) + F.nxn * ((2 * EJ + (q / 3) % 3) + F.nyn * (2 * EK + q / 9))];
+    for (int q = 0; q < 27; ++q) {
+      const unsigned mk = F.mask[(2 * EI + q % 3) + F.nxn * ((2 * EJ + (q / 3) % 3) + F.nyn * (2 * EK + q / 9))];
 #pragma unroll
-            for (int d = 0; d < 3; ++d) fixed[d] |= ((mk >> d) & 1u) << q;
-          }
+      for (int d = 0; d < 3; ++d) fixed[d] |= ((mk >> d) & 1u) << q;
+    }
+    double Ee[8];
 #pragma unroll
-          for (int c = 0; c < 8; ++c)
-            Ee[c] = E[(2 * EI + (c & 1)) + F.nx * ((2 * EJ + ((c >> 1) & 1)) + F.ny * (2 * EK + (c >> 2)))];
+    for (int c = 0; c < 8; ++c)
+      Ee[c] = E[(2 * EI + (c & 1)) + F.nx * ((2 * EJ + ((c >> 1) & 1)) + F.ny * (2 * EK + (c >> 2)))];
 #pragma unroll
-          for (int c = 0; c < 8; ++c) {
-            const int cx = c & 1, cy = (c >> 1) & 1, cz = c >> 2;
-            const int n0 = cx + 3 * cy + 9 * cz;  // the child's first node; its nodes: n0 + {0, 1, 3, 4, 9, 10, 12, 13}
-            if (!(((fixed[0] | fixed[1] | fixed[2]) >> n0) & 0x361bu)) {
-              const double* Gc = G + c * 576 + (3 * a) * 24 + 3 * b;
+    for (int c = 0; c < 8; ++c) {
+      const int cx = c & 1, cy = (c >> 1) & 1, cz = c >> 2;
+      const int n0 = cx + 3 * cy + 9 * cz;  // the child's first node; its nodes: n0 + {0, 1, 3, 4, 9, 10, 12, 13}
+      if (!(((fixed[0] | fixed[1] | fixed[2]) >> n0) & 0x361bu)) {
+        const double* Gc = G + c * 576 + (3 * a) * 24 + 3 * b;
 #pragma unroll
-              for (int ci = 0; ci < 3; ++ci)
+        for (int ci = 0; ci < 3; ++ci)
 #pragma unroll
-                for (int cj = 0; cj < 3; ++cj) blk[3 * ci + cj] += Ee[c] * Gc[ci * 24 + cj];
-            } else {  // masked child: P_c^T (M K0 M) P_c restricted to corners a, b
-              for (int p = 0; p < 8; ++p) {
-                const int px = p & 1, py = (p >> 1) & 1, pz = p >> 2;
-                const double wa = wt(cx + px, ax) * wt(cy + py, ay) * wt(cz + pz, az);
-                if (wa == 0.0) continue;
-                const int np = n0 + px + 3 * py + 9 * pz;
-                for (int q = 0; q < 8; ++q) {
-                  const int qx = q & 1, qy = (q >> 1) & 1, qz = q >> 2;
-                  const double wb = wt(cx + qx, bx) * wt(cy + qy, by) * wt(cz + qz, bz);
-                  if (wb == 0.0) continue;
-                  const int nq = n0 + qx + 3 * qy + 9 * qz;
-                  const double w = Ee[c] * wa * wb;
+          for (int cj = 0; cj < 3; ++cj) blk[3 * ci + cj] += Ee[c] * Gc[ci * 24 + cj];
+      } else {  // masked child: P_c^T (M K0 M) P_c restricted to corners a, b
+        for (int p = 0; p < 8; ++p) {
+          const int px = p & 1, py = (p >> 1) & 1, pz = p >> 2;
+          const double wa = wt(cx + px, ax) * wt(cy + py, ay) * wt(cz + pz, az);
+          if (wa == 0.0) continue;
+          const int np = n0 + px + 3 * py + 9 * pz;
+          for (int q = 0; q < 8; ++q) {
+            const int qx = q & 1, qy = (q >> 1) & 1, qz = q >> 2;
+            const double wb = wt(cx + qx, bx) * wt(cy + qy, by) * wt(cz + qz, bz);
+            if (wb == 0.0) continue;
+            const int nq = n0 + qx + 3 * qy + 9 * qz;
+            const double w = Ee[c] * wa * wb;
 #pragma unroll
-                  for (int ci = 0; ci < 3; ++ci)
+            for (int ci = 0; ci < 3; ++ci)
 #pragma unroll
-                    for (int cj = 0; cj < 3; ++cj)
-                      blk[3 * ci + cj] += (((fixed[ci] >> np) | (fixed[cj] >> nq)) & 1u)
-                                              ? 0.0
-                                              : w * Ke[(3 * p + ci) * 24 + 3 * q + cj];
-                }
-              }
-            }
+              for (int cj = 0; cj < 3; ++cj)
+                blk[3 * ci + cj] += (((fixed[ci] >> np) | (fixed[cj] >> nq)) & 1u)
+                                        ? 0.0
+                                        : w * Ke[(3 * p + ci) * 24 + 3 * q + cj];
           }
         }
       }
     }
+  }
+#pragma unroll
+  for (int q = 0; q < 9; ++q) part[side][q][lane] = blk[q];
+  __syncthreads();
+  if (side > 0 || t >= count) return;
+#pragma unroll
+  for (int q = 0; q < 9; ++q) {
+    double v = part[0][q][lane];
+#pragma unroll
+    for (int e = 1; e < 8; ++e) v += part[e][q][lane];
+    blk[q] = v;
   }
   store_block(C, m, m2, o, blk, S64, S32);
 }
@@ -521,7 +532,7 @@ void launch_galerkin_first(const Level& F, const Level& C, const double* E, cons
                            const uint8_t* flag, const int* list, int count, double* S64, float* S32, hipStream_t s) {
   k_galerkin_first<<<blocks_for(C.nn), kBlock, 0, s>>>(F, C, E, G + 8 * 576, flag, S64, S32);
   if (count > 0)
-    k_galerkin_first_masked<<<dim3((count + 63) / 64, 14), 64, 0, s>>>(F, C, E, G, Ke, list, count, S64, S32);
+    k_galerkin_first_masked<<<dim3((count + 63) / 64, 14), 512, 0, s>>>(F, C, E, G, Ke, list, count, S64, S32);
 }
 
 void launch_galerkin_coarsen(const Level& F, const Level& C, const double* Sf, double* S64, float* S32,
