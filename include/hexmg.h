@@ -78,8 +78,8 @@ extern "C" {
 /* Storage of the Galerkin coarse stencils read by binary32 V-cycles (hexmg_grid_desc.stencil_storage) */
 #define HEXMG_STENCIL_F32 0  /* binary32 (default) */
 #define HEXMG_STENCIL_BF16 1 /* bfloat16: half the bytes, 8 significand bits, binary32's exponent range */
-#define HEXMG_STENCIL_F16 2  /* binary16: half the bytes, 11 significand bits, each node's coefficients scaled by
-                                a power of two (kept per node) so that the largest is in [2^14, 2^15) */
+#define HEXMG_STENCIL_F16 2  /* binary16: half the bytes, 11 significand bits, each 3x3 block scaled by a power
+                                of two (kept per block) so that its largest coefficient is in [2^14, 2^15) */
 
 /* Coarse operators */
 #define HEXMG_COARSE_REDISCRETIZE 0 /* coarse element stiffness from the homogenized density (Sec. 4.2.2, default) */

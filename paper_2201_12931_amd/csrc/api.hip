@@ -373,7 +373,7 @@ size_t carve(hexmg_grid* g, char* base) {
       g->S64[l] = c.take<double>(nq);
       if (store == HEXMG_STENCIL_F32) g->S32[l] = c.take<float>(nq);  // binary32 K u at any precision
       if (v32 && store != HEXMG_STENCIL_F32) g->S16[l] = c.take<uint16_t>(nq);
-      if (v32 && store == HEXMG_STENCIL_F16) g->Sexp[l] = c.take<int8_t>(g->lv[l].nn);
+      if (v32 && store == HEXMG_STENCIL_F16) g->Sexp[l] = c.take<int8_t>((size_t)kStencilBlocks * g->lv[l].nn);
     }
   }
   return c.off + 256;

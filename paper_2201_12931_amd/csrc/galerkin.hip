@@ -21,11 +21,14 @@
 // Storage of the binary32 V-cycle's stencils: binary32, or 16 bits per
 // coefficient (half the bytes of the HBM-bound stencil sweep).  bfloat16 keeps
 // binary32's exponent range; binary16 keeps 3 more significand bits but not the
-// range (the coefficients span Emin..E0 times 2^l), so each node's stored
-// coefficients are scaled by a power of two that brings the largest magnitude
-// among them into [2^14, 2^15), and the sweep applies 2^-s to the sums over
-// them.  Both are rounded to nearest from the binary64 stencil (bfloat16
-// through binary32).
+// range (the coefficients span Emin..E0 times 2^l), so each stored 3x3 block is
+// scaled by a power of two of its own that brings the largest magnitude in it
+// into [2^14, 2^15), and the sweep applies 2^-s to the products with the block.  (One
+// power per node is not enough: a block is read by both nodes that it couples, and
+// under the scale of a stiff node its blocks towards a soft one -- the soft one's
+// largest -- lie in binary16's subnormals: off by 1.6e-3 of the soft node's largest
+// coefficient at Emin / E0 = 1e-9, by 0.45 at 1e-12, against 5e-4 by block.)  Both are
+// rounded to nearest from the binary64 stencil (bfloat16 through binary32).
 #include <hip/hip_bf16.h>
 #include <hip/hip_fp16.h>
 
@@ -347,7 +350,8 @@ __global__ __launch_bounds__(64) void k_galerkin_coarsen(Level F, Level C, const
 }
 
 // One node's stored binary64 coefficients to 16 bits: bfloat16 (STORE ==
-// HEXMG_STENCIL_BF16) or binary16 scaled by 2^s[n] (HEXMG_STENCIL_F16).
+// HEXMG_STENCIL_BF16) or binary16, block b of node n scaled by
+// 2^sexp[b * nn + n] (HEXMG_STENCIL_F16).
 template <int STORE>
 __global__ void k_stencil_to16(Level L, const double* __restrict__ S64, uint16_t* __restrict__ S16,
                                int8_t* __restrict__ sexp) {
@@ -360,16 +364,22 @@ __global__ void k_stencil_to16(Level L, const double* __restrict__ S64, uint16_t
     }
     return;
   }
-  double amax = 0.0;
-  for (int q = 0; q < kStencilCoefs; ++q) amax = fmax(amax, fabs(S64[(long long)q * L.nn + n]));
-  int e = 0;
-  if (amax > 0.0) (void)frexp(amax, &e);  // amax in [2^(e-1), 2^e)
-  const int sc = min(max(15 - e, -126), 126);  // amax * 2^sc in [2^14, 2^15)
-  sexp[n] = (int8_t)max(min(sc, 127), -127);
-  for (int q = 0; q < kStencilCoefs; ++q) {
-    const long long idx = (long long)q * L.nn + n;
-    const _Float16 h = (_Float16)ldexp(S64[idx], sexp[n]);
-    S16[idx] = __builtin_bit_cast(uint16_t, h);
+  for (int b = 0; b < kStencilBlocks; ++b) {
+    double v[9], amax = 0.0;
+#pragma unroll
+    for (int q = 0; q < 9; ++q) {
+      v[q] = S64[(long long)(9 * b + q) * L.nn + n];
+      amax = fmax(amax, fabs(v[q]));
+    }
+    int e = 0;
+    if (amax > 0.0) (void)frexp(amax, &e);  // amax in [2^(e-1), 2^e)
+    const int sc = min(max(15 - e, -126), 126);  // amax * 2^sc in [2^14, 2^15)
+    sexp[(long long)b * L.nn + n] = (int8_t)sc;
+#pragma unroll
+    for (int q = 0; q < 9; ++q) {
+      const _Float16 h = (_Float16)ldexp(v[q], sc);
+      S16[(long long)(9 * b + q) * L.nn + n] = __builtin_bit_cast(uint16_t, h);
+    }
   }
 }
 
@@ -390,8 +400,8 @@ __device__ inline float stencil_coef(Stored16<F16Tag> S, long long i) {
   return __half2float(__ushort_as_half(S.p[i]));
 }
 
-// The 2^-e of a binary16 row (|e| <= 126).
-__device__ inline float row_scale(int e) { return __int_as_float((127 - e) << 23); }
+// The 2^-e of a binary16 block (|e| <= 126).
+__device__ inline float block_scale(int e) { return __int_as_float((127 - e) << 23); }
 
 // y = A u from the stencil (MODE as the element kernels: 0 A u, 1 Jacobi
 // sweep, 2 residual).  A block takes 64 nodes; its wave W the offsets W, W + 4,
@@ -404,7 +414,7 @@ __device__ inline float row_scale(int e) { return __int_as_float((127 - e) << 23
 // bytes of the stored half: 78 us on level 1 of 256x128x128 in binary32 (120 us
 // with the whole stencil stored, one thread per node), and the levels under 10^4
 // nodes take 4.7 us (16.6 us).  SP: the coefficient array (T*, or
-// Stored16<tag> for the 16-bit storages); sexp: the binary16 rows' scale exponents
+// Stored16<tag> for the 16-bit storages); sexp: the binary16 blocks' scale exponents
 // (null otherwise).
 template <typename T, typename SP, bool SCALED, int W>
 __device__ __forceinline__ void stencil_wave(const Level& L, SP S, const int8_t* __restrict__ sexp,
@@ -427,7 +437,8 @@ __device__ __forceinline__ void stencil_wave(const Level& L, SP S, const int8_t*
     for (int q = 0; q < 9; ++q)
       cf[t][q] = o >= 13 ? stencil_coef(S, (long long)(9 * (o - 13) + q) * L.nn + n)
                          : stencil_coef(S, (long long)(9 * (13 - o) + 3 * (q % 3) + q / 3) * L.nn + m);
-    if constexpr (SCALED) sc[t] = row_scale(sexp[o >= 13 ? n : m]);
+    if constexpr (SCALED)
+      sc[t] = block_scale(sexp[o >= 13 ? (long long)(o - 13) * L.nn + n : (long long)(13 - o) * L.nn + m]);
   }
 #pragma unroll
   for (int c = 0; c < 3; ++c) a[c] = T(0);

@@ -475,7 +475,7 @@ void launch_volume_weights(long long n, const uint8_t* passive, int* count, doub
 // Galerkin coarse operators (galerkin.hip): the stored half of the 27-point block
 // stencils (offsets o = 13..26), coefficient (9 (o - 13) + 3 ci + cj) of node n at
 // S[(9 (o - 13) + 3 ci + cj) * nn + n].
-constexpr int kStencilCoefs = 126;
+constexpr int kStencilBlocks = 14, kStencilCoefs = 9 * kStencilBlocks;
 constexpr int kChildMatrices = 8 * 576 + 36 * 72;  // doubles of galerkin_child_matrices
 // level-1 nodes next to fixed fine DOFs: flag per node, their list; returns their
 // number (synchronises s), -1 on error
@@ -488,7 +488,7 @@ template <typename T>
 void launch_stencil(int mode, const Level& L, const T* S, const T* u, const T* f, const T* wd, T* y, int nrhs,
                     const int* act, hipStream_t s, const LaunchTimer& t = {});
 // The binary32 stencil sweep with 16-bit coefficients (store = HEXMG_STENCIL_BF16
-// or HEXMG_STENCIL_F16; sexp: binary16 rows' scale exponents), and the
+// or HEXMG_STENCIL_F16; sexp: binary16 blocks' scale exponents), and the
 // conversion of a binary64 stencil into that storage.
 void launch_stencil16(int store, int mode, const Level& L, const uint16_t* S16, const int8_t* sexp, const float* u,
                       const float* f, const float* wd, float* y, int nrhs, const int* act, hipStream_t s,
@@ -583,7 +583,7 @@ struct hexmg_grid {
   std::vector<double*> S64;
   std::vector<float*> S32;
   std::vector<uint16_t*> S16;  // 16-bit coefficients (stencil_storage != HEXMG_STENCIL_F32)
-  std::vector<int8_t*> Sexp;   // binary16 rows' scale exponents
+  std::vector<int8_t*> Sexp;   // binary16 blocks' scale exponents (kStencilBlocks per node)
   double* Gc = nullptr;
   uint8_t* gal_flag = nullptr;  // level-1 nodes next to fixed fine DOFs: flag, list and number of them
   int* gal_list = nullptr;
