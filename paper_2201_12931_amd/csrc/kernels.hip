@@ -311,7 +311,9 @@ __global__ void k_modulus_from_mean(Level F, Level C, const double* __restrict__
 
 // omega / diag(A) per node: the element stiffness of a cube has one diagonal entry
 // for all its DOFs, so a node's three components share theirs (fixed DOFs take
-// L.omega where the sweep is applied).  One value per node instead of three takes
+// L.omega where the sweep is applied to anything but zero there; a node with all three
+// fixed gets it here, as its elements may be void enough for omega / d to overflow
+// binary32, and inf times its zero right-hand side is NaN).  One value per node instead of three takes
 // 8 (16) of a binary32 (binary64) sweep's 53 (106) bytes per node away: the level-0 sweeps
 // are bound by their bytes, and the solve at 768x384x384 went from 128.4 to 123.2
 // ms, the binary64 one at 256x128x128 from 11.50 to 11.09.  The eight moduli are
@@ -320,6 +322,7 @@ __global__ void k_diag(Level L, const double* __restrict__ Ke, const double* __r
                        double* __restrict__ wd64, float* __restrict__ wd32) {
   const int n = blockIdx.x * kBlock + threadIdx.x;
   if (n >= L.nn) return;
+  const int mk = L.mask[n];
   int i, j, k;
   node_coords(L, n, i, j, k);
   double v[8];  // all eight requested before the first is added
@@ -334,7 +337,7 @@ __global__ void k_diag(Level L, const double* __restrict__ Ke, const double* __r
   double d = 0.0;
 #pragma unroll
   for (int a = 0; a < 8; ++a) d += v[a] * k0;
-  const double w = L.omega / d;
+  const double w = (mk & 7) == 7 ? L.omega : L.omega / d;
   if (wd64) wd64[n] = w;  // either output may be absent (the grid holds one precision)
   if (wd32) wd32[n] = (float)w;
 }
