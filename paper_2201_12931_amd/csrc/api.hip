@@ -1341,12 +1341,22 @@ int hexmg_apply_K(hexmg_grid_t g, int level, int dtype, const void* u, void* y, 
   if (nrhs > 65535) return fail(HEXMG_ERR_INVALID, "nrhs must be <= 65535");
   if (dtype == HEXMG_F32 && g->galerkin && level > 0 && !g->S32[level] && !g->S16[level])
     return fail(HEXMG_ERR_INVALID, "this grid holds no binary32 stencils (16-bit storage needs a binary32 V-cycle)");
-  if (dtype == HEXMG_F64)
-    gather<double>(g, kApply, level, (const double*)u, nullptr, nullptr, (double*)y, nrhs, s, true);
-  else if (dtype == HEXMG_F32)
-    gather<float>(g, kApply, level, (const float*)u, nullptr, nullptr, (float*)y, nrhs, s, true);
-  else
-    return fail(HEXMG_ERR_INVALID, "bad dtype");
+  if (dtype != HEXMG_F64 && dtype != HEXMG_F32) return fail(HEXMG_ERR_INVALID, "bad dtype");
+  // The right-hand sides of one launch: the streaming kernel's grid has z-chunks times
+  // right-hand sides along z, 65535 at the most (the choice of its chunks knows
+  // max_nrhs, not this call's nrhs).
+  const Level& L = g->lv[level];
+  const hexmg_grid::Choice& ch = (dtype == HEXMG_F64 ? g->choice64 : g->choice32)[level][kApply];
+  const bool stream_kernel = ch.kernel == HEXMG_KERNEL_STREAM && !(g->galerkin && level > 0);
+  const int most = stream_kernel ? 65535 / ((L.nzn + ch.zchunk - 1) / ch.zchunk) : nrhs;
+  for (int k = 0; k < nrhs; k += most) {
+    const int nb = std::min(most, nrhs - k);
+    const long long off = 3ll * L.nn * k;
+    if (dtype == HEXMG_F64)
+      gather<double>(g, kApply, level, (const double*)u + off, nullptr, nullptr, (double*)y + off, nb, s, true);
+    else
+      gather<float>(g, kApply, level, (const float*)u + off, nullptr, nullptr, (float*)y + off, nb, s, true);
+  }
   HIP_TRY(hipGetLastError());
   return 0;
 }
