@@ -317,8 +317,10 @@ int hexmg_element_matrix(double nu, double *Ke_host);
  * binary32) take a streaming shape by their size; on larger ones the choice is
  * made by timing the candidates (node-gather; every streaming shape with 1..128
  * planes per chunk -- a chunk of one plane requests all its inputs before any
- * arithmetic) with max_nrhs right-hand sides on the grid's stream during the first
- * successful hexmg_set_density, separately for K u, the sweep and the residual.
+ * arithmetic) with max_nrhs right-hand sides (no more than bring the level to 1.5e6
+ * nodes) on the grid's stream during the first successful hexmg_set_density, separately
+ * for K u, the sweep and the residual; a candidate that is far behind the fastest one
+ * after a few launches is timed no further.
  * V-cycles with two sweeps and re-discretized operators run levels of up to 6000
  * nodes (times max_nrhs) in fused steps of their own, a launch down and a launch up,
  * unless hexmg_set_kernel_choice was called for the level; K u still takes the choice reported here. */

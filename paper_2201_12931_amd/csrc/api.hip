@@ -7,6 +7,7 @@
 #include <functional>
 #include <string>
 
+#include "choose.h"
 #include "hexmg_impl.h"
 
 namespace hexmg {
@@ -552,30 +553,21 @@ int tune_level(hexmg_grid* g, int level, T* u, T* f, T* y, const T* wd, std::arr
   HIP_TRY(hipEventCreate(&e0));
   HIP_TRY(hipEventCreate(&e1));
   for (int mode = 0; mode < modes; ++mode) {
-    float best_stream = 1e30f, best_gather = 1e30f;
-    hexmg_grid::Choice bs{HEXMG_KERNEL_STREAM, 4, 0};
     const int reps = (long long)L.nn * nrhs < 400000 ? 12 : 3;
-    for (const auto& c : cand) {
-      float ms = 0.f;
-      auto timed = [&](int n) -> int {
-        HIP_TRY(hipEventRecord(e0, s));
-        for (int rep = 0; rep < n; ++rep) run(c, mode);
-        HIP_TRY(hipEventRecord(e1, s));
-        HIP_TRY(hipEventSynchronize(e1));
-        HIP_TRY(hipEventElapsedTime(&ms, e0, e1));
-        return 0;
-      };
-      // the first launch (cold, so up to half as long again) rules most candidates out
-      if (int e = timed(1)) return e;
-      if (ms * reps > 1.6f * std::min(best_stream, best_gather)) continue;
-      if (int e = timed(reps)) return e;
-      if (c.kernel == HEXMG_KERNEL_GATHER) {
-        best_gather = ms;
-      } else if (ms < best_stream) {
-        best_stream = ms;
-        bs = c;
-      }
-    }
+    auto timed = [&](int i, int n, float* t) -> int {
+      HIP_TRY(hipEventRecord(e0, s));
+      for (int rep = 0; rep < n; ++rep) run(cand[i], mode);
+      HIP_TRY(hipEventRecord(e1, s));
+      HIP_TRY(hipEventSynchronize(e1));
+      HIP_TRY(hipEventElapsedTime(t, e0, e1));
+      return 0;
+    };
+    std::vector<float> ms;
+    if (int e = time_candidates((int)cand.size(), reps, timed, &ms)) return e;
+    const float best_gather = ms.back();
+    const size_t at = std::min_element(ms.begin(), ms.end() - 1) - ms.begin();
+    const float best_stream = ms[at];
+    const hexmg_grid::Choice bs = cand[at];
     (*out)[mode] = (best_gather < 0.95f * best_stream) ? hexmg_grid::Choice{HEXMG_KERNEL_GATHER, 0, 0} : bs;
   }
   (void)hipEventDestroy(e0);
