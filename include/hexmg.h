@@ -123,7 +123,9 @@ typedef struct {
                            pre-smoothing sweep of each CG iteration's V-cycle forms the first
                            sweep from zero, (omega/D) r, as it loads its input, so the residual
                            update writes no first-sweep vector; 0: the residual update writes it.
-                           The two give bit-identical results. */
+                           The two give bit-identical results.  A finest level that takes the
+                           fused steps of the small levels (see hexmg_kernel_choice) forms the
+                           first sweep there with either value. */
 } hexmg_grid_desc;
 
 /* Fill *desc with the defaults (E0 1, Emin 1e-9, nu 0.3, penal 3, FP64, 2 sweeps,
@@ -197,7 +199,8 @@ int hexmg_solve(hexmg_grid_t grid, const double *f, double *u, int nrhs, double 
 /* S15: solve several grids (distinct objects, each after a successful
  * hexmg_set_density) together: grid i solves nrhs[i] <= its max_nrhs
  * right-hand sides f[i] -> u[i] (device, [nrhs[i]][N_i] doubles) exactly as
- * hexmg_solve would (same kernels, same arithmetic, bit for bit).  All grids
+ * hexmg_solve would with the cooperative coarse cycle off (hexmg_set_coarse_cycle;
+ * same kernels, same arithmetic, bit for bit).  All grids
  * run on `stream` in lockstep: each PCG step and each V-cycle step (sweep,
  * residual, restriction, coarsest solve, prolongation) of all grids is one
  * kernel launch whose workgroups look up their grid in a task table passed
@@ -229,8 +232,10 @@ int hexmg_compliance_sensitivity(hexmg_grid_t grid, const double *f, const doubl
  * |c_e - c_i|) over the in-domain elements of an nx*ny*nz grid (element
  * order), 1 < rmin <= 8.  adjoint = 0: out = (H in) / Hs, Hs = H 1;
  * adjoint != 0: out = H (in / Hs), the transpose (tmp: device, nx*ny*nz
- * doubles of scratch, distinct from in and out; unused and may be NULL for
- * the forward filter).  in and out must not overlap.  Asynchronous. */
+ * doubles of scratch, distinct from in and out; may be NULL for the forward
+ * filter, and is written for rmin > 4 only, or for ny or nz > 65535: the adjoint
+ * of smaller radii divides by Hs as it loads).  in and out must not overlap.
+ * Asynchronous. */
 int hexmg_filter(int nx, int ny, int nz, double rmin, int adjoint, const double *in, double *out,
                  double *tmp, void *stream);
 
@@ -241,9 +246,10 @@ int hexmg_filter(int nx, int ny, int nz, double rmin, int adjoint, const double 
  * process ends) instead of a caller buffer, and the call allocates nothing.
  * Same arguments and results as hexmg_filter without tmp; the adjoint returns
  * -1 for more than 2^22 elements (the forward filter needs no scratch and has
- * hexmg_filter's limits).  Every adjoint call on a GPU shares that GPU's
- * array, so adjoint calls that overlap on one GPU (different streams or host
- * threads without ordering) race.  Asynchronous. */
+ * hexmg_filter's limits).  The size limit holds for every radius, but only the
+ * adjoint calls whose intermediate is stored (rmin > 4, see hexmg_filter) use the
+ * array: those share it with every other on the same GPU, so they race where they
+ * overlap (different streams or host threads without ordering).  Asynchronous. */
 int hexmg_filter_noalloc(int nx, int ny, int nz, double rmin, int adjoint, const double *in, double *out,
                          void *stream);
 
@@ -338,7 +344,9 @@ int hexmg_set_kernel_choice(hexmg_grid_t grid, int level, int dtype, int kernel,
 /* The coarse part of the V-cycle (Alg. 3) may run as one cooperative launch
  * (a grid-stride kernel whose phases -- sweeps, residual, restriction,
  * coarsest solve, prolongation -- are separated by grid-wide barriers) instead
- * of one launch per step; the arithmetic is that of the node-gather kernels.
+ * of one launch per step; the arithmetic is that of the node-gather kernels, so
+ * results equal the step launches' bit for bit where those are node-gathers and to
+ * rounding otherwise.
  * *level = first level of that launch (1 .. levels-2) or 0 when every level is
  * launched step by step; *blocks = its workgroup count.  By default the choice
  * is made by timing both forms on the grid's stream during the first
@@ -359,7 +367,9 @@ int hexmg_set_coarse_cycle(hexmg_grid_t grid, int dtype, int level, int blocks);
  * by events on its stream; hexmg_profile_query returns the number of launches and their
  * total milliseconds since the last reset (synchronises the grid's last
  * stream).  Families: "apply_f64", "apply_f32", "smooth_f64", "smooth_f32",
- * "residual_f64", "residual_f32". */
+ * "residual_f64", "residual_f32".  A finest level that takes the fused steps of the
+ * small levels (see hexmg_kernel_choice) has no sweep or residual launches in its
+ * solves. */
 int hexmg_profile_enable(hexmg_grid_t grid, int enable);
 int hexmg_profile_query(hexmg_grid_t grid, const char *family, int *launches, double *ms);
 

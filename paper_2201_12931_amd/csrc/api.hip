@@ -488,7 +488,10 @@ void launch_choice(hexmg_grid* g, const hexmg_grid::Choice& ch, int mode, int le
 // Timed back to back, a binary32 (binary64) product takes 3.4 (3.9) us with one row
 // per thread, whatever the size up to 4e4 nodes, and the tile of two rows is the
 // faster one from 1e5 to 4e5 (7.1 against 8.0 us at 2.8e5); in binary64 the timed
-// choice varies there.  The differences between the other candidates are within
+// choice varies there.  Solves of ten iterations with this choice at level 0 against
+// every uniform choice of four chunks and all shapes there: the best one, or within 1.5%
+// of it (the repeatability), at 2e4 to 9.9e4 nodes in binary64 and 4e4 to 3.9e5 in binary32.
+// The differences between the other candidates are within
 // the noise of timing such launches, and grids that share a choice share their
 // batched launches.  Right-hand sides count as nodes (they are more workgroups of one launch).
 bool choice_by_size(const Level& L, bool f32, int max_nrhs, hexmg_grid::Choice* c) {
@@ -754,11 +757,15 @@ void wait_coarse(hexmg_grid* g, hipStream_t s) {
 // Whether level l takes the fused steps of the small levels (tile.hip): two
 // sweeps, re-discretized operators, a kernel choice left to the library, and up to
 // kTileNodes nodes (counted per right-hand side).  With the limit at 6000 a state
-// at 32x16x16 (binary64) takes 1140 us against 1253 step by step, one at 128x64x64
-// (mixed) 2189 against about 2300.  At 1e4 nodes the repeated work of the halos has caught
-// up with the launches: 1146 us at 32x16x16, and eight uneven grids solved together,
-// whose step launches are shared, 3798 against 3426 us.  Level 0 of the public V-cycle
-// (maskin), whose right-hand side may be non-zero at fixed DOFs, is launched step by step.
+// at 32x16x16 (binary64) took 1140 us against 1253 step by step, one at 128x64x64
+// (mixed) 2189 against about 2300.  What holds the limit there is the batch: eight uneven
+// grids solved together, whose step launches are shared, took 3798 us with the limit at
+// 1e4 against 3426, as grids of one level fall on both sides of it.  A grid solved alone
+// would gain from fused steps up to 1e4 nodes too: ten iterations with one level of 6069,
+// 7225, 8381 or 9537 nodes take 672, 656, 668, 669 us in binary64 with the limit at 1e4, 710,
+// 681, 728, 729 with it at 6000; mixed 592, 585, 597, 593 and 697, 690, 684, 677.  Level 0 of the
+// public V-cycle (maskin), whose right-hand side may be non-zero at fixed DOFs, is
+// launched step by step.
 constexpr long long kTileNodes = 6000;
 template <typename T>
 bool use_tiles(const hexmg_grid* g, int l, bool maskin = false) {

@@ -5,8 +5,11 @@
 // This kernel runs levels ls .. L-1 of the cycle -- the remaining pre-sweeps,
 // residual, restriction, the coarsest solve, prolongation and post-sweeps --
 // as phases of one grid-stride kernel separated by grid-wide barriers.  Each
-// phase does exactly what the corresponding separate kernel does (the per-node
-// functions are shared), in the same order, so the cycle is unchanged.
+// phase does exactly what the corresponding separate node-gather kernel does (the
+// per-node functions are shared), in the same order: the cycle equals the one launched
+// step by step bit for bit where its levels take that kernel, and to rounding where
+// they take the streaming kernel or the fused small-level steps (tile.hip), whose
+// sums associate differently.
 //
 // The launch is cooperative (hipLaunchCooperativeKernel): the runtime only
 // starts it when every workgroup is resident at once, which is what makes the
