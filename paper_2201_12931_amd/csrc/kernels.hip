@@ -317,7 +317,8 @@ __global__ void k_modulus_from_mean(Level F, Level C, const double* __restrict__
 // 8 (16) of a binary32 (binary64) sweep's 53 (106) bytes per node away: the level-0 sweeps
 // are bound by their bytes, and the solve at 768x384x384 went from 128.4 to 123.2
 // ms, the binary64 one at 256x128x128 from 11.50 to 11.09.  The eight moduli are
-// requested together: 0.63 ms at 768x384x384, 0.97 as eight loads each behind its own test.
+// requested together: 0.67 ms at 768x384x384 (0.63 without the support bits), 0.97 as
+// eight loads each behind its own test.
 __global__ void k_diag(Level L, const double* __restrict__ Ke, const double* __restrict__ E,
                        double* __restrict__ wd64, float* __restrict__ wd32) {
   const int n = blockIdx.x * kBlock + threadIdx.x;

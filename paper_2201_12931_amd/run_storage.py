@@ -61,12 +61,13 @@ def main():
             code, inf = grid.solve(f_d, u, rtol=args.rtol, maxit=args.maxit)
             ms.append(inf[0]["ms_solve"])
             info = inf[0]
-        nq = sum(126 * (g.nx // 2 ** l + 1) * (g.ny // 2 ** l + 1) * (g.nz // 2 ** l + 1) for l in range(1, levels))
-        word = {hexmg.STENCIL_F32: 4, hexmg.STENCIL_BF16: 2, hexmg.STENCIL_F16: 2}[store]
+        nodes = sum((g.nx // 2 ** l + 1) * (g.ny // 2 ** l + 1) * (g.nz // 2 ** l + 1) for l in range(1, levels))
+        # bytes per node: 126 coefficients; binary16 also holds an exponent for each of its 14 blocks
+        per_node = {hexmg.STENCIL_F32: 4 * 126, hexmg.STENCIL_BF16: 2 * 126, hexmg.STENCIL_F16: 2 * 126 + 14}[store]
         r = {"status": code, "iterations": info["iterations"], "rel_res_true": info["rel_res_true"],
              "compliance": info["compliance"], "solve_ms": sorted(ms)[len(ms) // 2], "setup_ms": setup_ms,
              "workspace_bytes": grid.workspace.numel(),
-             "stencil_bytes_vcycle": nq * word if precision != hexmg.FP64 else nq * 8}
+             "stencil_bytes_vcycle": nodes * (per_node if precision != hexmg.FP64 else 8 * 126)}
         grid.close()
         print(f"run_storage: {name}: {r}", file=sys.stderr, flush=True)
         return r, u
