@@ -12,13 +12,22 @@
 // fills only the tiles up to row K + wb (from the bottom: down to row K - wb).  So
 // while K' - K > wb a step sweeps two pivots, K from the top and K' from the
 // bottom: A_KK' is still zero, and D of the two together is block diagonal.  It
-// leaves alone what neither reaches.  The last wb + 1 pivots at most are swept
-// one to a step on all tiles.
+// leaves alone what neither reaches.  The wb + 1 pivots at most that are left between
+// them, and then the last two tiles' pivots, are swept one to a step on all tiles.
+//
+// Why the last two tiles wait: the pivot swept last is the whole structure condensed onto
+// its block, the softest and least accurate one.  Ending between the two fronts cost
+// digits on slender grids, whose blocks are whole rows of nodes along the length: the
+// inverse was 37 times (20x1x2 elements), 26 (24x1x2) and 4 times (20x2x2) as far from
+// the exact one as in the natural order (geometric means over 12 to 14 densities, with the
+// 64 terms of an update added one by one); ending at the last tiles, as the natural order
+// does, and summing the terms on their own, 0.86, 1.4 and 1.2 times, and 0.78 over
+// 213 designs on 16 grid shapes.  It costs one step at most.
 //
 // A step on few tiles is bound by its serial chain (launch, one round of loads, two
 // 64^3 products at the binary64 matrix rate, the next pivot tile's inverse: 18 us, the
 // inverse 8 of them), one on many by the products.  Measured, pack to unpack: 675
-// unknowns (wb = 3) 143 us in 7 steps, 1911 (5) 385 us in 18, 2304 (7) 508 us in 22; in order
+// unknowns (wb = 3) 158 us in 8 steps, 1911 (5) 401 us in 19, 2304 (7) 521 us in 23; in order
 // on all tiles 205, 714 and 885 us in 11, 30 and 36 steps (and 290, 1960 and 2200 us as a
 // full Gauss-Jordan whose tiles took three rounds of loads).
 //
@@ -41,6 +50,7 @@ namespace hexmg {
 namespace {
 
 constexpr int kTile = kGJBlock * kGJBlock;  // elements of a tile
+constexpr int kLastPivots = 2;  // tiles whose pivots are swept after all others
 typedef double d2 __attribute__((ext_vector_type(2)));
 typedef double d4 __attribute__((ext_vector_type(4)));
 
@@ -145,14 +155,16 @@ __device__ inline void invert_tile(InverseLds& lds, d4 (&y)[4], double* __restri
 #pragma unroll
       for (int i = 1; i < 4; ++i) y[i] = d4{0.0, 0.0, 0.0, 0.0};
     }
+    d4 z[3];  // summed on their own, as in sweep_tile
+#pragma unroll
+    for (int i = 0; i < 3; ++i) z[i] = d4{0.0, 0.0, 0.0, 0.0};
 #pragma unroll
     for (int ks = 0; ks < 4; ++ks)
 #pragma unroll
-      for (int i = 1; i < 4; ++i)
-        y[i] = __builtin_amdgcn_mfma_f64_16x16x4f64(row[(s + i) & 3][ks * 64 + l], -W[ks], y[i], 0, 0, 0);
-    y[0] = y[1];
-    y[1] = y[2];
-    y[2] = y[3];
+      for (int i = 0; i < 3; ++i)
+        z[i] = __builtin_amdgcn_mfma_f64_16x16x4f64(row[(s + i + 1) & 3][ks * 64 + l], W[ks], z[i], 0, 0, 0);
+#pragma unroll
+    for (int i = 0; i < 3; ++i) y[i] = y[i + 1] - z[i];
     y[3] = W;
   }
 #pragma unroll
@@ -293,12 +305,19 @@ __device__ __forceinline__ void sweep_tile(SweepOperands& lds, int K, int I, int
 #pragma unroll
     for (int t = 0; t < 4; ++t) y[t] = x[t];
   } else {
+    // the 64 terms are summed on their own: added one by one to an element much larger than
+    // they are, each would round at its size
+    d4 z[4];
+#pragma unroll
+    for (int t = 0; t < 4; ++t) z[t] = d4{0.0, 0.0, 0.0, 0.0};
 #pragma unroll
     for (int ks = 0; ks < 16; ++ks)
 #pragma unroll
       for (int t = 0; t < 4; ++t)
-        y[t] = __builtin_amdgcn_mfma_f64_16x16x4f64(lds.op[1][t * 1024 + ks * 64 + l], -x[ks >> 2][ks & 3], y[t], 0,
-                                                    0, 0);
+        z[t] = __builtin_amdgcn_mfma_f64_16x16x4f64(lds.op[1][t * 1024 + ks * 64 + l], x[ks >> 2][ks & 3], z[t], 0, 0,
+                                                    0);
+#pragma unroll
+    for (int t = 0; t < 4; ++t) y[t] -= z[t];
   }
 }
 
@@ -405,18 +424,23 @@ void launch_spd_inverse(int n, int band, double* A, double* scratch, hipStream_t
   double* T = scratch;
   double* P[2] = {T + tri(nt, 0), T + tri(nt, 0) + 2ll * nt * kTile};  // by parity, then side
   double* D[2] = {P[1] + 2ll * nt * kTile, P[1] + (2ll * nt + 2) * kTile};
-  // pivots from both ends while they are not coupled, then the rest in order
-  auto next = [&](int lo, int hi) {  // lo..hi are left
-    Pivots p{{lo <= hi ? lo : -1, hi - lo > wb ? hi : -1}};
-    return p;
+  // pivots lo and hi while they are not coupled, then what is left between them in
+  // order, then the last tiles
+  int lo = 0, rest = std::max(nt - kLastPivots, 0), hi = rest - 1;
+  auto next = [&]() -> Pivots {
+    if (lo <= hi) return Pivots{{lo, hi - lo > wb ? hi : -1}};
+    return Pivots{{rest < nt ? rest : -1, -1}};
   };
-  int lo = 0, hi = nt - 1;
-  Pivots p = next(lo, hi);
+  Pivots p = next();
   k_sweep_pack<<<tiles, kBlock, 0, s>>>(n, nt, p, A, T, P[0], D[0]);
   for (int k = 0; p.K[0] >= 0; ++k) {
-    ++lo;
-    if (p.K[1] >= 0) --hi;
-    const Pivots q = next(lo, hi);
+    if (lo <= hi) {
+      ++lo;
+      if (p.K[1] >= 0) --hi;
+    } else {
+      ++rest;
+    }
+    const Pivots q = next();
     k_sweep_step<<<tiles, kBlock, 0, s>>>(nt, wb, p, q, T, P[k & 1], D[k & 1], P[(k + 1) & 1], D[(k + 1) & 1]);
     p = q;
   }
